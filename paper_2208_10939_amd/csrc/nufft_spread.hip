@@ -4,6 +4,9 @@
 // nufft.hip for the transform it belongs to and the kernels around it).
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
+#include <type_traits>
+
 #include "nufft_common.h"
 #include "rsim_internal.h"
 #include "rsim_launch.h"
@@ -79,59 +82,70 @@ __device__ __forceinline__ void even2_cells(float2 (&acc)[kNuSlots], float2 c0, 
 // source covers NCELL or fewer cells (its count is floor(2 reach) or one more, NCELL at
 // least the larger), so a block may reach up to four cells past the last the runs
 // guarantee inside the window; those are dropped (their Gaussian weights are below
-// psi(W/2) for every channel). The blocks sit behind a chain of independent scalar bit
-// tests rather than a switch: every block then updates the window registers in place,
-// where the merge of a switch's cases costs register copies of the untouched cells.
-// First cell of a source's block: the lowest cell within `reach` of the source's
-// position for the wave's first channel, clamped to the blocks the chain holds (the
-// runs keep every channel's cells inside the window, so a clamp never drops one of them).
-// lo_lanes holds the unclamped cell of the record's source at s[3 j] in lane j (j < 3).
-__device__ __forceinline__ int block_start(int lo_lanes, int j) {
-  const int s = __builtin_amdgcn_readlane(lo_lanes, j);
-  return s < 0 ? 0 : s > 22 ? 22 : s;
+// psi(W/2) for every channel). The blocks sit behind independent scalar bit tests rather
+// than a switch: every block then updates the window registers in place, where the merge
+// of a switch's cases costs register copies of the untouched cells. The tests come in two
+// levels, groups of four blocks first: a test that fails is a taken branch, and 23 of them
+// a source left the waves waiting for their instructions.
+constexpr int kNuTopStart = 22;  // the last block start
+template <int NCELL, int S0, typename F>
+__device__ __forceinline__ void try_block(uint32_t bit, F &&f) {
+  if constexpr (S0 <= kNuTopStart) {
+    if (bit & (1u << S0)) f(std::integral_constant<int, S0>{});
+  }
+}
+template <int NCELL, typename F>
+__device__ __forceinline__ void select_block(int s_lo, F &&f) {
+  const uint32_t bit = 1u << s_lo;
+#define RSIM_NU_GROUP(G)                          \
+  if (bit & (0xFu << (4 * G))) {                  \
+    try_block<NCELL, 4 * G>(bit, f);              \
+    try_block<NCELL, 4 * G + 1>(bit, f);          \
+    try_block<NCELL, 4 * G + 2>(bit, f);          \
+    try_block<NCELL, 4 * G + 3>(bit, f);          \
+  }
+  RSIM_NU_GROUP(0) RSIM_NU_GROUP(1) RSIM_NU_GROUP(2) RSIM_NU_GROUP(3) RSIM_NU_GROUP(4)
+  RSIM_NU_GROUP(5)
+#undef RSIM_NU_GROUP
+  static_assert(kNuTopStart < 24, "every start has a block");
 }
 
-#define RSIM_NU_CASES(X) \
-  X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) \
-  X(16) X(17) X(18) X(19) X(20) X(21) X(22)
+// First Gaussian weight of a block and its first step, for a lane's source at pos.
+__device__ __forceinline__ void first_cell(int s_lo, float pos, float nc, float &u0, float &gw,
+                                           float &rho) {
+  u0 = static_cast<float>(s_lo) - pos;
+  gw = __builtin_amdgcn_exp2f(nc * u0 * u0);
+  rho = __builtin_amdgcn_exp2f(nc * fmaf(2.0f, u0, 1.0f));
+}
 
 template <int NCELL>
 __device__ __forceinline__ void spread_point(float2 (&acc)[kNuSlots], float2 cw, float pos,
                                              int s_lo, float nc, float q_ratio) {
-  const float u0 = static_cast<float>(s_lo) - pos;
-  const float gw = __builtin_amdgcn_exp2f(nc * u0 * u0);
-  const float rho = __builtin_amdgcn_exp2f(nc * fmaf(2.0f, u0, 1.0f));
-  const uint32_t bit = static_cast<uint32_t>(s_lo) < 32u ? 1u << s_lo : 0u;  // none: no cell
-#define RSIM_NU_POINT(S) \
-  if (bit & (1u << S)) point_cells<S, NCELL>(acc, cw, gw, rho, q_ratio);
-  RSIM_NU_CASES(RSIM_NU_POINT)
-#undef RSIM_NU_POINT
+  float u0, gw, rho;
+  first_cell(s_lo, pos, nc, u0, gw, rho);
+  select_block<NCELL>(s_lo, [&](auto s0) __attribute__((always_inline)) {
+    point_cells<s0(), NCELL>(acc, cw, gw, rho, q_ratio);
+  });
 }
 
 template <int NCELL>
 __device__ __forceinline__ void spread_even2(float2 (&acc)[kNuSlots], float2 c0, float2 c2,
                                              float pos, int s_lo, float nc, float q_ratio) {
-  const float u0 = static_cast<float>(s_lo) - pos;
-  const float gw = __builtin_amdgcn_exp2f(nc * u0 * u0);
-  const float rho = __builtin_amdgcn_exp2f(nc * fmaf(2.0f, u0, 1.0f));
-  const uint32_t bit = static_cast<uint32_t>(s_lo) < 32u ? 1u << s_lo : 0u;  // none: no cell
-#define RSIM_NU_EVEN2(S) \
-  if (bit & (1u << S)) even2_cells<S, NCELL>(acc, c0, c2, u0, gw, rho, q_ratio);
-  RSIM_NU_CASES(RSIM_NU_EVEN2)
-#undef RSIM_NU_EVEN2
+  float u0, gw, rho;
+  first_cell(s_lo, pos, nc, u0, gw, rho);
+  select_block<NCELL>(s_lo, [&](auto s0) __attribute__((always_inline)) {
+    even2_cells<s0(), NCELL>(acc, c0, c2, u0, gw, rho, q_ratio);
+  });
 }
 
 template <int NCELL, int NC>
 __device__ __forceinline__ void spread_poly(float2 (&acc)[kNuSlots], const float2 (&c)[NC],
                                             float pos, int s_lo, float nc, float q_ratio) {
-  const float u0 = static_cast<float>(s_lo) - pos;
-  const float gw = __builtin_amdgcn_exp2f(nc * u0 * u0);
-  const float rho = __builtin_amdgcn_exp2f(nc * fmaf(2.0f, u0, 1.0f));
-  const uint32_t bit = static_cast<uint32_t>(s_lo) < 32u ? 1u << s_lo : 0u;  // none: no cell
-#define RSIM_NU_POLY(S) \
-  if (bit & (1u << S)) poly_cells<S, NCELL, NC>(acc, c, u0, gw, rho, q_ratio);
-  RSIM_NU_CASES(RSIM_NU_POLY)
-#undef RSIM_NU_POLY
+  float u0, gw, rho;
+  first_cell(s_lo, pos, nc, u0, gw, rho);
+  select_block<NCELL>(s_lo, [&](auto s0) __attribute__((always_inline)) {
+    poly_cells<s0(), NCELL, NC>(acc, c, u0, gw, rho, q_ratio);
+  });
 }
 
 // (1 - j 2 pi B m'^2) on the modes is F + j eps F'' on the grid (F = psi P): coefficient
@@ -153,52 +167,75 @@ __device__ __forceinline__ void intra_coeffs(const float2 (&c)[NI], float2 (&o)[
   }
 }
 
+// The part of a record that its channels and cells need, read through scalar loads.
+struct NuHead {
+  double g1;
+  float rt, rr, t0, frac;
+  int32_t cell, kind;
+  float s[10];
+};
+static_assert(offsetof(NuRecF<false>, s) - offsetof(NuRecF<false>, g1) == offsetof(NuHead, s) &&
+                  offsetof(NuRecF<false>, rt) - offsetof(NuRecF<false>, g1) ==
+                      offsetof(NuHead, rt) &&
+                  offsetof(NuRecF<false>, kind) - offsetof(NuRecF<false>, g1) ==
+                      offsetof(NuHead, kind) &&
+                  offsetof(NuRecF<true>, g1) == offsetof(NuRecF<false>, g1),
+              "the head's fields are consecutive");
+
+// What a record's channels owe to one element e of their two: u.a, the remainder of the
+// path difference and the path difference itself (see the header of nufft.hip).
+struct ElemTerm {
+  double s;
+  float e, dR;
+};
+
 }  // namespace
 
 // One workgroup per (chirp, run) and up to four 64-channel groups (blockIdx.z counts
-// further groups); lane = channel. The run's records (read once per wave through scalar
-// loads, the next one in flight while the current one is spread) add their sources into a
-// register window of kNuSlots cells starting at the run's base cell; the window is written
-// to part[chirp][run][channel][kNuSlots]. The kernel waits mostly on latencies (record
-// loads, transcendental results, the branch chain), so occupancy pays: the stop-and-hop
-// form is held to five waves per SIMD (96 registers), the other to four.
+// further groups); lane = channel. A run's records are taken batch by batch:
+//  - staging: a lane per (record, element) forms what the record's channels owe to that Tx
+//    or Rx element, into LDS: P + Q elements for P Q channels (28 for 192 on the 12 x 16
+//    array), where every lane forming its own channel's took a fifth of the kernel's
+//    instructions; then a lane per record the first cells of the record's blocks;
+//  - spread: per record a lane joins its two elements' terms and adds the record's sources
+//    into its register window of kNuSlots cells, which starts at the run's base cell and
+//    goes to part[chirp][run][channel][kNuSlots] at the run's end.
+// Bound by the waves' latencies (LDS and scalar loads, transcendentals, the blocks' branches)
+// at the five waves per SIMD that 96 registers leave, the window taking 64 of them; four
+// waves: 95.5 against 88.3 ms. On the 1M-triangle intersection (82M records, 192 channels) the
+// element terms and the two-level block tests took it from 102.8 to 88.3 ms.
 template <bool INTRA, int NCELL>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(INTRA ? 4 : 5, 8)))
 nufft_spread_kernel(
     DevScene sc0, RadarConst rc, NuShape ns, const double *elem,
     const NuRecF<INTRA> *__restrict__ sorted, const int4 *__restrict__ runs,
     const int32_t *__restrict__ n_runs, float2 *__restrict__ part, NuBatch bt) {
+  extern __shared__ __align__(16) unsigned char spread_smem[];
   const int nl = blockIdx.y;
   const int run = blockIdx.x;
   if (run >= load_uniform(n_runs + nl)) return;  // whole workgroup
   const NuWork w = nu_work(sc0, ns, bt, nl);
-  const int grp = static_cast<int>(blockIdx.z) * 4 + static_cast<int>(threadIdx.x >> 6);
+  const int E = rc.P + rc.Q, batch = ns.spread_batch;
+  ElemTerm *term = reinterpret_cast<ElemTerm *>(spread_smem);             // [batch][E]
+  double *off = reinterpret_cast<double *>(term + batch * E);              // [E][3]
+  float *rdot = reinterpret_cast<float *>(off + 3 * E);                    // [batch][E] (INTRA)
+  int32_t *all_starts = reinterpret_cast<int32_t *>(rdot + (INTRA ? batch * E : 0));
+  for (int i = threadIdx.x; i < 3 * E; i += blockDim.x) {
+    const int k = i % 3;
+    off[i] = elem[i] - (i < 3 * rc.P ? rc.tx_c[k] : rc.rx_c[k]);
+  }
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int grp = static_cast<int>(blockIdx.z) * 4 + wave;
   const int lane = threadIdx.x & 63;
   const int O = rc.P * rc.Q;
-  if (grp * 64 >= O) return;  // whole wave
+  const bool wave_on = grp * 64 < O;
   const int4 rr = load_uniform(runs + w.run + run);
   const int o = grp * 64 + lane;
   const bool on = o < O;
-  // this lane's element offsets from the phase centres
-  double at[3], ar[3];
-  float aat, aar, atf[3], arf[3];
-  {
-    const int oc = on ? o : grp * 64;  // idle lanes: the wave's first channel
-    const int p = oc / rc.Q, q = oc - p * rc.Q;
-    double st = 0.0, sr = 0.0;
-    for (int k = 0; k < 3; ++k) {
-      at[k] = elem[3 * p + k] - rc.tx_c[k];
-      ar[k] = elem[3 * (rc.P + q) + k] - rc.rx_c[k];
-      st += at[k] * at[k];
-      sr += ar[k] * ar[k];
-    }
-    aat = static_cast<float>(st);
-    aar = static_cast<float>(sr);
-    for (int k = 0; k < 3; ++k) {
-      atf[k] = static_cast<float>(at[k]);
-      arf[k] = static_cast<float>(ar[k]);
-    }
-  }
+  const int oc = on ? o : wave_on ? grp * 64 : 0;  // idle lanes: the wave's first channel
+  const int p = oc / rc.Q, q = rc.P + oc % rc.Q;
+  const int p_first = grp * 64 / rc.Q, q_first = rc.P + grp * 64 % rc.Q;
+  int32_t *starts_of = all_starts + wave * batch;  // [waves][batch]
   const float inv_c0 = static_cast<float>(1.0 / kC0), inv_fs = static_cast<float>(1.0 / rc.fs);
   const float df_fs = static_cast<float>(rc.df / rc.fs);
   const float half_m = 0.5f * rc.M, quarter_m2 = 0.25f * rc.M * rc.M, m_f = static_cast<float>(rc.M);
@@ -211,92 +248,142 @@ nufft_spread_kernel(
   const float kappa = static_cast<float>(ns.kappa);
   const float g2 = static_cast<float>(0.5 * rc.slope / (kC0 * kC0));
   const float reach = static_cast<float>(ns.wave_d) + 0.5f * kNuWidth;
+  // the delay within the chirp moves a channel's source by (A + B M) n_g cells, of which the
+  // record's frac holds ext[5]
+  const auto doppler_shift = [&](float tdot, double g1, float ext5, float &A, float &B)
+                                 __attribute__((always_inline)) {
+    const float fmt = static_cast<float>(g1 * kC0 - (rc.M / 2) * rc.df);
+    A = fmt * tdot * inv_fs;
+    B = df_fs * tdot;
+    return fmaf(B, m_f, A) * ngf - ext5;
+  };
   float2 acc[kNuSlots];
 #pragma unroll
   for (int s = 0; s < kNuSlots; ++s) acc[s] = {0.0f, 0.0f};
-  NuRecF<INTRA> nxt = load_uniform(srec + rr.x);
-  for (int i = rr.x; i < rr.y; ++i) {
-    const NuRecF<INTRA> r = nxt;
-    nxt = load_uniform(srec + (i + 1 < rr.y ? i + 1 : i));
-    if (r.kind == 0) continue;  // wave-uniform
-    // position of the phase-centre path in the window
-    const float rel_c = static_cast<float>(r.cell - rr.z) + r.frac;
-    // this channel's path difference dL = -(s_t + s_r) + e_t + e_r, amplitude, phase
-    // and grid position
-    const double st = r.ut[0] * at[0] + r.ut[1] * at[1] + r.ut[2] * at[2];
-    const double sr = r.ur[0] * ar[0] + r.ur[1] * ar[1] + r.ur[2] * ar[2];
-    const double ps = (st + sr) * r.g1;  // turns, up to ~25
-    const float pr = static_cast<float>(ps - rint(ps));
-    const float sft = static_cast<float>(st), sfr = static_cast<float>(sr);
-    const float ht = fmaf(-sft, sft, aat), hr = fmaf(-sfr, sfr, aar);
-    const float rdt = __builtin_amdgcn_rcpf(fmaf(-2.0f, sft, 2.0f * r.rt));
-    const float rdr = __builtin_amdgcn_rcpf(fmaf(-2.0f, sfr, 2.0f * r.rr));
-    const float qt = ht * rdt, qr = hr * rdr;
-    const float et = qt * fmaf(-qt, rdt, 1.0f), er = qr * fmaf(-qr, rdr, 1.0f);
-    const float dRt = et - sft, dRr = er - sfr;
-    const float dL = dRt + dRr;
-    float t = (r.t0 - pr) + fmaf(static_cast<float>(r.g1), et + er, -g2 * dL * dL);
-    float xr = fmaf(kappa, dL, rel_c);
-    float eps = 0.0f;  // B n_g^2 / (2 pi): weight of F'' for the B m'^2 term
-    if constexpr (INTRA) {
-      // this channel's tau' (first order in the sample time), its Doppler shift relative
-      // to the record's and the constant phase A M/2 + B M^2/4
-      const float vat = r.ext[0] * atf[0] + r.ext[1] * atf[1] + r.ext[2] * atf[2];
-      const float var = r.ext[0] * arf[0] + r.ext[1] * arf[1] + r.ext[2] * arf[2];
-      const float rdt_dot = fmaf(r.rt, r.ext[3], -vat) * __builtin_amdgcn_rcpf(r.rt + dRt);
-      const float rdr_dot = fmaf(r.rr, r.ext[4], -var) * __builtin_amdgcn_rcpf(r.rr + dRr);
-      const float tdot = (rdt_dot + rdr_dot) * inv_c0;
-      const float fmt = static_cast<float>(r.g1 * kC0 - (rc.M / 2) * rc.df);
-      const float A = fmt * tdot * inv_fs, B = df_fs * tdot;
-      t += fmaf(A, half_m, B * quarter_m2);
-      xr += fmaf(B, m_f, A) * ngf - r.ext[5];
-      eps = B * eps_scale;
-    }
-    t -= rintf(t);
-    // the wave's first channel: every channel of the wave lies within wave_d cells of it
-    const float x0 = __builtin_bit_cast(
-        float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, xr)));
-    const float amp = __builtin_amdgcn_rcpf((r.rt + dRt) * (r.rr + dRr));
-    const float qx = __builtin_amdgcn_cosf(t) * amp, qy = -__builtin_amdgcn_sinf(t) * amp;
-    const int n_pts = r.kind == 1 ? 3 : r.kind == 2 ? 1 : 0;
-    // the block starts of the record's sources at s[0], s[3], s[6], one per lane (lanes 0,
-    // 1, 2) in one pass instead of one wave-wide pass each
-    const float off_l = lane == 0 ? r.s[0] : lane == 1 ? r.s[3] : r.s[6];
-    const int lo_lanes = static_cast<int>(ceilf((x0 - off_l) - reach));
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      if (j < n_pts) {
-        const float off = r.s[3 * j];
-        const float2 cw = {qx * r.s[3 * j + 1] - qy * r.s[3 * j + 2],
-                           qx * r.s[3 * j + 2] + qy * r.s[3 * j + 1]};
-        // cells some channel reaches: |s - (x_o - off)| <= W/2 with |x_o - x0| <= wave_d,
-        // NCELL of them from s_lo
-        const int s_lo = block_start(lo_lanes, j);
-        if constexpr (INTRA) {
-          // (1 - j 2 pi B m'^2) on a point's modes: cw (1 - j eps / s^2) + j eps cw / s^4 x^2
-          // (intra_coeffs of one coefficient; its linear term is zero)
-          const float e2 = eps * inv_s2, e4 = e2 * inv_s2;
-          const float2 c0 = {fmaf(e2, cw.y, cw.x), fmaf(-e2, cw.x, cw.y)};
-          const float2 c2 = {-e4 * cw.y, e4 * cw.x};
-          spread_even2<NCELL>(acc, c0, c2, xr - off, s_lo, nc, q_ratio);
-        } else {
-          spread_point<NCELL>(acc, cw, xr - off, s_lo, nc, q_ratio);
-        }
+  for (int b0 = rr.x; b0 < rr.y; b0 += batch) {
+    const int nb = min(batch, rr.y - b0);
+    __syncthreads();  // the offsets are in; the last batch's readers are done
+    for (int i = threadIdx.x; i < nb * E; i += blockDim.x) {
+      const int rec = i / E, e = i - rec * E;
+      const NuRecF<INTRA> *r = srec + b0 + rec;
+      const bool tx = e < rc.P;
+      const double *u = tx ? r->ut : r->ur;
+      const double a[3] = {off[3 * e], off[3 * e + 1], off[3 * e + 2]};
+      double aa = 0.0;
+      for (int k = 0; k < 3; ++k) aa += a[k] * a[k];
+      const double s = u[0] * a[0] + u[1] * a[1] + u[2] * a[2];
+      const float dist = tx ? r->rt : r->rr;
+      const float sf = static_cast<float>(s);
+      const float h = fmaf(-sf, sf, static_cast<float>(aa));
+      const float rd = __builtin_amdgcn_rcpf(fmaf(-2.0f, sf, 2.0f * dist));
+      const float qd = h * rd;
+      const float ed = qd * fmaf(-qd, rd, 1.0f);
+      const float dR = ed - sf;
+      term[i] = {s, ed, dR};
+      if constexpr (INTRA) {
+        const float af[3] = {static_cast<float>(a[0]), static_cast<float>(a[1]),
+                             static_cast<float>(a[2])};
+        const float va = r->ext[0] * af[0] + r->ext[1] * af[1] + r->ext[2] * af[2];
+        rdot[i] = fmaf(dist, tx ? r->ext[3] : r->ext[4], -va) * __builtin_amdgcn_rcpf(dist + dR);
       }
     }
-    if (r.kind >= 2) {
-      const float off = r.s[3];
-      float2 cq[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-        cq[k] = {qx * r.s[4 + 2 * k] - qy * r.s[5 + 2 * k], qx * r.s[5 + 2 * k] + qy * r.s[4 + 2 * k]};
-      const int s_lo = block_start(lo_lanes, 1);
+    __syncthreads();
+    if (!wave_on) continue;
+    // a lane per record: the first cells of its blocks in this wave (sources at s[0], s[3],
+    // s[6]): the lowest cell within `reach` of the source's position for the wave's first
+    // channel, clamped to the blocks there are (the runs keep every channel's cells inside the
+    // window, so a clamp never drops one of them). Every channel of the wave lies within
+    // wave_d cells of the first.
+    if (lane < nb) {
+      const NuRecF<INTRA> *r = srec + b0 + lane;
+      const float dL = term[lane * E + p_first].dR + term[lane * E + q_first].dR;
+      float x0 = fmaf(kappa, dL, static_cast<float>(r->cell - rr.z) + r->frac);
       if constexpr (INTRA) {
-        float2 c5[5];
-        intra_coeffs(cq, c5, eps, inv_s2);
-        spread_poly<NCELL>(acc, c5, xr - off, s_lo, nc, q_ratio);
-      } else {
-        spread_poly<NCELL>(acc, cq, xr - off, s_lo, nc, q_ratio);
+        const float tdot = (rdot[lane * E + p_first] + rdot[lane * E + q_first]) * inv_c0;
+        float A, B;
+        x0 += doppler_shift(tdot, r->g1, r->ext[5], A, B);
+      }
+      int32_t starts = 0;
+      for (int j = 0; j < 3; ++j) {
+        const int lo = static_cast<int>(ceilf((x0 - r->s[3 * j]) - reach));
+        starts |= min(max(lo, 0), kNuTopStart) << (8 * j);
+      }
+      starts_of[lane] = starts;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const auto *heads = reinterpret_cast<const unsigned char *>(srec + b0) +
+                        offsetof(NuRecF<INTRA>, g1);
+    const auto head = [&](int i) {
+      return load_uniform(reinterpret_cast<const NuHead *>(heads + i * sizeof(NuRecF<INTRA>)));
+    };
+    const ElemTerm *tp = term + p, *tq = term + q;
+    NuHead nxt = head(0);
+    for (int i = 0; i < nb; ++i) {
+      const NuHead r = nxt;
+      nxt = head(i + 1 < nb ? i + 1 : i);
+      const ElemTerm T = tp[i * E], R = tq[i * E];
+      const uint32_t starts = __builtin_amdgcn_readfirstlane(starts_of[i]);
+      if (r.kind == 0) continue;  // wave-uniform
+      // this channel's path difference dL = -(s_t + s_r) + e_t + e_r, amplitude, phase and
+      // grid position
+      const float rel_c = static_cast<float>(r.cell - rr.z) + r.frac;
+      const double ps = (T.s + R.s) * r.g1;  // turns, up to ~25
+      const float pr = static_cast<float>(ps - rint(ps));
+      const float dL = T.dR + R.dR;
+      float t = (r.t0 - pr) + fmaf(static_cast<float>(r.g1), T.e + R.e, -g2 * dL * dL);
+      float xr = fmaf(kappa, dL, rel_c);
+      float eps = 0.0f;  // B n_g^2 / (2 pi): weight of F'' for the B m'^2 term
+      if constexpr (INTRA) {
+        // this channel's tau' (first order in the sample time), its Doppler shift relative
+        // to the record's and the constant phase A M/2 + B M^2/4
+        const float tdot = (rdot[i * E + p] + rdot[i * E + q]) * inv_c0;
+        float A, B;
+        const float shift = doppler_shift(
+            tdot, r.g1, load_uniform(&srec[b0 + i].ext[5]), A, B);
+        t += fmaf(A, half_m, B * quarter_m2);
+        xr += shift;
+        eps = B * eps_scale;
+      }
+      t -= rintf(t);
+      const float amp = __builtin_amdgcn_rcpf((r.rt + T.dR) * (r.rr + R.dR));
+      const float qx = __builtin_amdgcn_cosf(t) * amp, qy = -__builtin_amdgcn_sinf(t) * amp;
+      const int n_pts = r.kind == 1 ? 3 : r.kind == 2 ? 1 : 0;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        if (j < n_pts) {
+          const float off_j = r.s[3 * j];
+          const float2 cw = {qx * r.s[3 * j + 1] - qy * r.s[3 * j + 2],
+                             qx * r.s[3 * j + 2] + qy * r.s[3 * j + 1]};
+          // cells some channel reaches: |s - (x_o - off)| <= W/2 with |x_o - x0| <= wave_d,
+          // NCELL of them from s_lo
+          const int s_lo = static_cast<int>((starts >> (8 * j)) & 31u);
+          if constexpr (INTRA) {
+            // (1 - j 2 pi B m'^2) on a point's modes: cw (1 - j eps / s^2) + j eps cw / s^4 x^2
+            // (intra_coeffs of one coefficient; its linear term is zero)
+            const float e2 = eps * inv_s2, e4 = e2 * inv_s2;
+            const float2 c0 = {fmaf(e2, cw.y, cw.x), fmaf(-e2, cw.x, cw.y)};
+            const float2 c2 = {-e4 * cw.y, e4 * cw.x};
+            spread_even2<NCELL>(acc, c0, c2, xr - off_j, s_lo, nc, q_ratio);
+          } else {
+            spread_point<NCELL>(acc, cw, xr - off_j, s_lo, nc, q_ratio);
+          }
+        }
+      }
+      if (r.kind >= 2) {
+        const float off_j = r.s[3];
+        float2 cq[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+          cq[k] = {qx * r.s[4 + 2 * k] - qy * r.s[5 + 2 * k], qx * r.s[5 + 2 * k] + qy * r.s[4 + 2 * k]};
+        const int s_lo = static_cast<int>((starts >> 8) & 31u);
+        if constexpr (INTRA) {
+          float2 c5[5];
+          intra_coeffs(cq, c5, eps, inv_s2);
+          spread_poly<NCELL>(acc, c5, xr - off_j, s_lo, nc, q_ratio);
+        } else {
+          spread_poly<NCELL>(acc, cq, xr - off_j, s_lo, nc, q_ratio);
+        }
       }
     }
   }
@@ -308,6 +395,19 @@ nufft_spread_kernel(
     dst[s] = make_float4(acc[2 * s].x, acc[2 * s].y, acc[2 * s + 1].x, acc[2 * s + 1].y);
 }
 
+// Records staged together: 16 KB of element terms at most, 32 records where they fit.
+int nufft_spread_batch(int elements) {
+  int b = 32;
+  while (b > 1 && b * elements * static_cast<int>(sizeof(ElemTerm)) > (16 << 10)) b /= 2;
+  return b;
+}
+
+size_t nufft_spread_smem_bytes(int elements, int batch, int waves, bool intra) {
+  return batch * (elements * (sizeof(ElemTerm) + (intra ? sizeof(float) : 0)) +
+                  waves * sizeof(int32_t)) +
+         elements * 3 * sizeof(double);
+}
+
 namespace {
 
 template <bool INTRA>
@@ -315,17 +415,18 @@ hipError_t launch_spread_t(const DevScene &sc, const RadarConst &rc, const NuSha
                            const double *elem, const NuRecF<INTRA> *recs, const int4 *runs,
                            const int32_t *n_runs, float2 *part, const NuBatch &bt, dim3 grid,
                            dim3 blk, int ncell, hipStream_t s) {
+  const size_t lds = nufft_spread_smem_bytes(rc.P + rc.Q, ns.spread_batch, blk.x / 64, INTRA);
   switch (ncell) {
     case 14:
-      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 14>), grid, blk, 0, s, sc, rc, ns, elem,
+      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 14>), grid, blk, lds, s, sc, rc, ns, elem,
                          recs, runs, n_runs, part, bt);
       break;
     case 16:
-      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 16>), grid, blk, 0, s, sc, rc, ns, elem,
+      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 16>), grid, blk, lds, s, sc, rc, ns, elem,
                          recs, runs, n_runs, part, bt);
       break;
     case 20:
-      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 20>), grid, blk, 0, s, sc, rc, ns, elem,
+      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 20>), grid, blk, lds, s, sc, rc, ns, elem,
                          recs, runs, n_runs, part, bt);
       break;
     default:
@@ -336,13 +437,15 @@ hipError_t launch_spread_t(const DevScene &sc, const RadarConst &rc, const NuSha
 
 }  // namespace
 
-hipError_t launch_nufft_spread(const DevScene &sc, const RadarConst &rc, const NuShape &ns,
+hipError_t launch_nufft_spread(const DevScene &sc, const RadarConst &rc, const NuShape &ns0,
                                const double *elem, const void *srec, const int4 *runs,
                                const int32_t *n_runs, float2 *part, const NuBatch &bt,
                                hipStream_t s) {
   const int O = rc.P * rc.Q;
   const int groups = (O + 63) / 64;
   const int per_block = groups < 4 ? groups : 4;
+  NuShape ns = ns0;
+  ns.spread_batch = nufft_spread_batch(rc.P + rc.Q);
   dim3 sgrid(static_cast<unsigned>(ns.max_runs), static_cast<unsigned>(ns.n_chirps),
              static_cast<unsigned>((groups + 3) / 4));
   const dim3 blk(64 * per_block);
