@@ -5,12 +5,17 @@
 // All of it is small next to the facet sum: the integrated map and the CFAR are
 // HBM/LDS bound (one pass over the cube, then LDS tiles with a periodic halo), the
 // angle transform runs one workgroup per detected cell.
+#include <algorithm>
+
 #include "fft_common.h"
 #include "rsim.h"
 
 namespace rsim {
 
-// P[c][r] = sum_o rdm[c][o][r] over the O channels, in channel order.
+// P[c][r] = sum_o rdm[c][o][r] over the O channels, in channel order. HBM-bound: a thread
+// keeps kIntegrateBatch channels' loads in flight before their ordered adds (one load at a
+// time left the kernel waiting on memory: 192 channels of 256 x 512 cells 63 -> 22 us).
+constexpr int kIntegrateBatch = 16;
 __global__ void __launch_bounds__(256) integrate_kernel(const float *rdm, float *P, int O,
                                                         int64_t NM, int64_t cubes) {
   const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -18,7 +23,15 @@ __global__ void __launch_bounds__(256) integrate_kernel(const float *rdm, float 
   const int64_t c = idx / NM, r = idx - c * NM;
   const float *src = rdm + c * O * NM + r;
   float s = 0.0f;
-  for (int o = 0; o < O; ++o) s += src[o * NM];
+  int o = 0;
+  for (; o + kIntegrateBatch <= O; o += kIntegrateBatch) {
+    float v[kIntegrateBatch];
+#pragma unroll
+    for (int k = 0; k < kIntegrateBatch; ++k) v[k] = src[(o + k) * NM];
+#pragma unroll
+    for (int k = 0; k < kIntegrateBatch; ++k) s += v[k];
+  }
+  for (; o < O; ++o) s += src[o * NM];
   P[idx] = s;
 }
 
@@ -81,38 +94,64 @@ __global__ void __launch_bounds__(256) cfar_kernel(const float *P, int N, int M,
   }
 }
 
-// Row-major list of the detected cells of one cube (first max_points), and the count.
+// Row-major list of the detected cells of one cube (first max_points), and the count. One
+// workgroup a cube, kListCells consecutive cells a thread and step: a step costs a barrier and
+// a round trip to memory whatever it covers (131072 cells: 133 us at one cell a thread with
+// three barriers a step, 18 at 16 cells, 13 at 64).
+constexpr int kListCells = 64;
 __global__ void __launch_bounds__(1024) det_list_kernel(const uint8_t *det, int64_t NM,
                                                         int max_points, int32_t *list,
                                                         int32_t *count) {
-  __shared__ int32_t wave_tot[16];
-  __shared__ int32_t s_base;
+  __shared__ int32_t wave_tot[2][16];
   const int64_t c = blockIdx.x;
   const uint8_t *d = det + c * NM;
   int32_t *out = list + c * max_points;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int waves = blockDim.x >> 6;
-  if (threadIdx.x == 0) s_base = 0;
-  __syncthreads();
-  for (int64_t k0 = 0; k0 < NM; k0 += blockDim.x) {
-    const int64_t k = k0 + threadIdx.x;
-    const bool f = k < NM && d[k] != 0;
-    const uint64_t bal = __ballot(f);
-    const int before = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) wave_tot[wv] = __popcll(bal);
-    __syncthreads();
-    int off = s_base;
-    for (int w = 0; w < wv; ++w) off += wave_tot[w];
-    if (f && off + before < max_points) out[off + before] = static_cast<int32_t>(k);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int tot = 0;
-      for (int w = 0; w < waves; ++w) tot += wave_tot[w];
-      s_base += tot;
+  const bool aligned = (reinterpret_cast<uintptr_t>(d) & 15) == 0;  // a thread's cells start at a multiple of 16
+  int base = 0, buf = 0;
+  const int64_t step = static_cast<int64_t>(blockDim.x) * kListCells;
+  for (int64_t k0 = 0; k0 < NM; k0 += step, buf ^= 1) {
+    const int64_t k = k0 + static_cast<int64_t>(threadIdx.x) * kListCells;
+    uint64_t hits = 0;  // bit j: cell k + j is detected
+    if (aligned && k + kListCells <= NM) {
+      uint4 v[kListCells / 16];
+#pragma unroll
+      for (int q = 0; q < kListCells / 16; ++q) v[q] = reinterpret_cast<const uint4 *>(d + k)[q];
+#pragma unroll
+      for (int q = 0; q < kListCells / 16; ++q) {
+        const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+        if ((w[0] | w[1] | w[2] | w[3]) == 0) continue;
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+          hits |= ((w[j >> 2] >> (8 * (j & 3))) & 0xFFu) ? 1ull << (16 * q + j) : 0ull;
+      }
+    } else {
+      for (int j = 0; j < kListCells; ++j)
+        if (k + j < NM && d[k + j]) hits |= 1ull << j;
     }
+    const int mine = __popcll(hits);
+    int upto = mine;  // over the wave's lanes up to this one
+    for (int w = 1; w < 64; w <<= 1) {
+      const int v = __shfl_up(upto, w);
+      if (lane >= w) upto += v;
+    }
+    if (lane == 63) wave_tot[buf][wv] = upto;
     __syncthreads();
+    int off = base + upto - mine;
+    for (int w = 0; w < waves; ++w) {
+      const int v = wave_tot[buf][w];
+      off += w < wv ? v : 0;
+      base += v;
+    }
+    while (hits) {
+      const int j = __ffsll(static_cast<unsigned long long>(hits)) - 1;
+      hits &= hits - 1;
+      if (off < max_points) out[off] = static_cast<int32_t>(k + j);
+      ++off;
+    }
   }
-  if (threadIdx.x == 0) count[c] = s_base;
+  if (threadIdx.x == 0) count[c] = base;
 }
 
 struct AngleParams {
@@ -236,9 +275,11 @@ __device__ inline uint4 philox4x32_10(uint4 x, uint2 k) {
       k.x += 0x9E3779B9u;
       k.y += 0xBB67AE85u;
     }
-    const uint32_t hi0 = __umulhi(0xD2511F53u, x.x), lo0 = 0xD2511F53u * x.x;
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, x.z), lo1 = 0xCD9E8D57u * x.z;
-    x = make_uint4(hi1 ^ x.y ^ k.x, lo1, hi0 ^ x.w ^ k.y, lo0);
+    // one 64-bit product where the high and the low half cost a quarter-rate multiply each
+    const uint64_t p0 = static_cast<uint64_t>(0xD2511F53u) * x.x;
+    const uint64_t p1 = static_cast<uint64_t>(0xCD9E8D57u) * x.z;
+    x = make_uint4(static_cast<uint32_t>(p1 >> 32) ^ x.y ^ k.x, static_cast<uint32_t>(p1),
+                   static_cast<uint32_t>(p0 >> 32) ^ x.w ^ k.y, static_cast<uint32_t>(p0));
   }
   return x;
 }
@@ -268,33 +309,37 @@ __global__ void __launch_bounds__(256) power_partial_kernel(const C *h, int64_t 
   if (threadIdx.x == 0) part[c * kPowerBlocks + b] = s[0];
 }
 
-// Per cube: the per-part noise standard deviation sqrt(mean |H|^2 / snr / 2).
-__global__ void noise_scale_kernel(const double *part, int64_t n, int64_t cubes, double inv_snr,
-                                   double *scale) {
-  const int64_t c = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (c >= cubes) return;
+// Per cube (one wave): the per-part noise standard deviation sqrt(mean |H|^2 / snr / 2).
+__global__ void __launch_bounds__(64) noise_scale_kernel(const double *part, int64_t n,
+                                                         double inv_snr, double *scale) {
+  const int64_t c = blockIdx.x;
   double s = 0.0;
-  for (int b = 0; b < kPowerBlocks; ++b) s += part[c * kPowerBlocks + b];
-  scale[c] = sqrt(0.5 * (s / static_cast<double>(n)) * inv_snr);
+  for (int b = threadIdx.x; b < kPowerBlocks; b += 64) s += part[c * kPowerBlocks + b];
+  for (int w = 32; w > 0; w >>= 1) s += __shfl_xor(s, w);
+  if (threadIdx.x == 0) scale[c] = sqrt(0.5 * (s / static_cast<double>(n)) * inv_snr);
 }
+
+constexpr unsigned kNoiseCubes = 1024;  // cubes of a launch's grid; each block loops on
 
 template <typename C>
 __global__ void __launch_bounds__(256) add_noise_kernel(C *h, int64_t n, int64_t cubes,
                                                         const double *scale, uint2 key) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= cubes * n) return;
-  const int64_t c = idx / n, i = idx - c * n;
-  const uint4 x = philox4x32_10(make_uint4(static_cast<uint32_t>(i), static_cast<uint32_t>(i >> 32),
-                                           static_cast<uint32_t>(c), 0u), key);
-  const double u1 = (static_cast<double>(x.x) + 0.5) * 0x1p-32;
-  const double u2 = (static_cast<double>(x.y) + 0.5) * 0x1p-32;
-  const double r = sqrt(-2.0 * log(u1)) * scale[c];
-  double sn, cs;
-  sincospi(2.0 * u2, &sn, &cs);
-  C v = h[idx];
-  v.x += r * cs;
-  v.y += r * sn;
-  h[idx] = v;
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  for (int64_t c = blockIdx.y; c < cubes; c += gridDim.y) {
+    const uint4 x = philox4x32_10(make_uint4(static_cast<uint32_t>(i),
+                                             static_cast<uint32_t>(i >> 32),
+                                             static_cast<uint32_t>(c), 0u), key);
+    const double u1 = (static_cast<double>(x.x) + 0.5) * 0x1p-32;
+    const double u2 = (static_cast<double>(x.y) + 0.5) * 0x1p-32;
+    const double r = sqrt(-2.0 * log(u1)) * scale[c];
+    double sn, cs;
+    sincospi(2.0 * u2, &sn, &cs);
+    C v = h[c * n + i];
+    v.x += r * cs;
+    v.y += r * sn;
+    h[c * n + i] = v;
+  }
 }
 
 // ---- host launches -----------------------------------------------------------------------
@@ -340,20 +385,21 @@ hipError_t launch_add_noise(int precision, void *echo, int64_t n, int64_t cubes,
   const double inv_snr = pow(10.0, -snr_db / 10.0);
   const uint2 key = make_uint2(static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32));
   const dim3 pg(kPowerBlocks, static_cast<unsigned>(cubes));
-  const unsigned grid = static_cast<unsigned>((cubes * n + 255) / 256);
+  const dim3 grid(static_cast<unsigned>((n + 255) / 256),
+                  std::min(kNoiseCubes, static_cast<unsigned>(cubes)));
   if (precision) {
     hipLaunchKernelGGL(power_partial_kernel<double2>, pg, dim3(256), 0, s,
                        static_cast<const double2 *>(echo), n, part);
-    hipLaunchKernelGGL(noise_scale_kernel, dim3(static_cast<unsigned>((cubes + 63) / 64)), dim3(64),
-                       0, s, part, n, cubes, inv_snr, scale);
-    hipLaunchKernelGGL(add_noise_kernel<double2>, dim3(grid), dim3(256), 0, s,
+    hipLaunchKernelGGL(noise_scale_kernel, dim3(static_cast<unsigned>(cubes)), dim3(64), 0, s,
+                       part, n, inv_snr, scale);
+    hipLaunchKernelGGL(add_noise_kernel<double2>, grid, dim3(256), 0, s,
                        static_cast<double2 *>(echo), n, cubes, scale, key);
   } else {
     hipLaunchKernelGGL(power_partial_kernel<float2>, pg, dim3(256), 0, s,
                        static_cast<const float2 *>(echo), n, part);
-    hipLaunchKernelGGL(noise_scale_kernel, dim3(static_cast<unsigned>((cubes + 63) / 64)), dim3(64),
-                       0, s, part, n, cubes, inv_snr, scale);
-    hipLaunchKernelGGL(add_noise_kernel<float2>, dim3(grid), dim3(256), 0, s,
+    hipLaunchKernelGGL(noise_scale_kernel, dim3(static_cast<unsigned>(cubes)), dim3(64), 0, s,
+                       part, n, inv_snr, scale);
+    hipLaunchKernelGGL(add_noise_kernel<float2>, grid, dim3(256), 0, s,
                        static_cast<float2 *>(echo), n, cubes, scale, key);
   }
   return hipGetLastError();
