@@ -460,6 +460,7 @@ EchoShape echo_shape(const rsim_ctx *ctx, const RadarConst &rc, int mb, int max_
   sh.B_w = std::max(1, std::min({blocks_needed, max_threads / sh.O_w, max_blocks}));
   sh.M_t = sh.B_w * mb;
   sh.m_tiles = (rc.M + sh.M_t - 1) / sh.M_t;
+  sh.B_s = sh.B_w;
   sh.n_compute = (sh.O_w * sh.B_w + 63) / 64 * 64;
   sh.two_pi_slope = 2.0 * kPi * rc.slope;
   return sh;
@@ -472,6 +473,34 @@ EchoShape forward_shape(const rsim_ctx *ctx, const RadarConst &rc, int precision
   while (sh.B_w > 1 && echo_smem_bytes(precision, mb, ft, sh) > ctx->max_lds)
     sh = echo_shape(ctx, rc, mb, kMaxComputeThreads, sh.B_w - 1);
   return sh;
+}
+
+// Plain launches of the default tiles with CUs to spare are cut finer: a workgroup takes one
+// block of sh.M_t's, and a thread a chunk of it. Taken is the first cut whose workgroups have a
+// CU each: 64 channels and 16-sample chunks (FP64: 8), else 192 channels and 32 (8); else the
+// shape stays as it is. A finer cut repeats the staging of a tile (FP64 geometry and phases)
+// in more workgroups, so it loses once they share CUs. Facet sum on MI355X, 192 channels x 256
+// samples: 4 chirps x 1.5k facets 530 us whole, 370 (192, 32), 303 (64, 16: 48 workgroups); 48
+// chirps x 60k facets 21.6 ms whole, 15.7 (192, 32: 192 workgroups), 36.6 (64, 16: 576). FP64,
+// 4 channels: 449 -> 133 us. The sample tiles stay the same (the facet integral's phases start
+// at theirs), so the sums are the same bits.
+EchoShape spread_shape(const rsim_ctx *ctx, const RadarConst &rc, const EchoShape &whole,
+                       int precision, int mb) {
+  const int chunks[2] = {precision ? 8 : 16, precision ? 8 : 32};
+  const int widths[2] = {64, kMaxComputeThreads / 2};
+  for (int k = 0; k < 2; ++k) {
+    EchoShape sh = whole;
+    const int tiles = (sh.O + widths[k] - 1) / widths[k];
+    sh.O_w = (sh.O + tiles - 1) / tiles;
+    sh.o_tiles = (sh.O + sh.O_w - 1) / sh.O_w;
+    sh.B_s = 1;
+    sh.chunk = chunks[k];
+    sh.n_compute = (sh.O_w * (mb / sh.chunk) + 63) / 64 * 64;
+    if (static_cast<int64_t>(rc.N) * sh.m_tiles * sh.B_w * sh.o_tiles <= ctx->cu_count &&
+        echo_smem_bytes(precision, mb, 16, sh) <= ctx->max_lds)
+      return sh;
+  }
+  return whole;
 }
 
 // Largest cross-term phase the matrix-core sum may drop: each term then carries a relative
@@ -740,6 +769,12 @@ SumPlan plan_sum(const rsim_ctx *ctx, const RadarConst &rc, const rsim_opts &o, 
   } else {
     pl.sh = forward_shape(ctx, rc, o.precision, pl.ts.mb, pl.ts.ft);
     pl.batch_key = pl.ts.mb;
+    // the default tiles, whether by default or tuned; a tile that is asked for is kept
+    const bool fallback = pl.ts.mb == (o.precision ? 16 : 64) && pl.ts.ft == (o.precision ? 8 : 16);
+    if (fallback && !o.tile_m && !o.tile_f && !o.persistent) {
+      pl.sh = spread_shape(ctx, rc, pl.sh, o.precision, pl.ts.mb);
+      if (pl.sh.chunk) pl.ts.ft = 16;
+    }
   }
   return pl;
 }
@@ -1587,7 +1622,7 @@ int32_t rsim_synthesize(rsim_ctx *ctx, const int32_t *scene_ids, int32_t n_scene
     }
   }
   const TunedShape ts = pl.ts;
-  if (!pl.matrix && !pl.nufft && !echo_variant_exists(o.precision, ts.mb, ts.ft))
+  if (!pl.matrix && !pl.nufft && !pl.sh.chunk && !echo_variant_exists(o.precision, ts.mb, ts.ft))
     return fail(ctx, RSIM_EINVAL, "no facet-sum variant with tile_m=%d tile_f=%d", ts.mb, ts.ft);
   if ((rc = need_device(ctx))) return rc;
   if (pl.nufft) {

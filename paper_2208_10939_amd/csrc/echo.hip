@@ -20,6 +20,12 @@
 // each element's phasor at every block start. One workgroup barrier per tile hands the
 // buffers over. Block starts are re-seeded from FP64 phases, so a phasor recurrence
 // never runs more than MB steps.
+//
+// Few chirps leave CUs without a workgroup, and a thread's serial chain (facets x MB samples)
+// is then the kernel's time. The cut forms (sh.chunk) give a workgroup one block of 64 or 192
+// channels and a thread a chunk of CH samples of it, whose phasors start from the block's by
+// the same steps: the same bits from up to 6 times the workgroups and MB / CH times the
+// threads. The host's spread_shape holds the rule and what both sides measured.
 #include "echo_common.h"
 
 namespace rsim {
@@ -41,14 +47,15 @@ struct EchoLayout {
     b = up(b + (kRotated ? sizeof(GLin) * FT : 0));
     // offsets inside one tile buffer
     size_t t = 0;
+    const size_t m_s = static_cast<size_t>(sh.B_s) * MB;  // samples of the workgroup
     G = t;
-    t += sizeof(C) * FT * sh.M_t;
+    t += sizeof(C) * FT * m_s;
     G1 = t;
-    t += kRotated ? sizeof(C) * FT * sh.M_t : 0;
+    t += kRotated ? sizeof(C) * FT * m_s : 0;
     U = t;
-    t += sizeof(C) * FT * sh.E * sh.B_w;
+    t += sizeof(C) * FT * sh.E * sh.B_s;
     rat = t;
-    t += sizeof(C) * FT * sh.E * sh.B_w;
+    t += sizeof(C) * FT * sh.E * sh.B_s;
     off = t;
     t = up(t + sizeof(R) * FT * sh.E);
     buf[0] = b;
@@ -62,10 +69,10 @@ struct EchoLayout {
 template <typename R, int MB, int FT>
 struct EchoTile {
   using C = typename Cx<R>::T;
-  C *G;    // [FT][M_t]
-  C *G1;   // [FT][M_t]: G (-j)^(m mod 4), for quarter-turn-rotated recurrences (FP32)
-  C *U;    // [B_w][FT][E]
-  C *rat;  // [B_w][FT][E]: per-sample phasor step of each block
+  C *G;    // [FT][B_s MB]
+  C *G1;   // [FT][B_s MB]: G (-j)^(m mod 4), for quarter-turn-rotated recurrences (FP32)
+  C *U;    // [B_s][FT][E]
+  C *rat;  // [B_s][FT][E]: per-sample phasor step of each block
   R *off;  // [FT][E]
 };
 
@@ -108,13 +115,15 @@ __device__ inline void wave_lds_sync() {
 }
 
 // Staging of one tile (entries t0 .. t0 + nf - 1 of chirp n) by the staging waves,
-// st = staging thread index in [0, kStagingThreads).
+// st = staging thread index in [0, kStagingThreads): sample tile from m_tile0 on, the blocks
+// blk0 .. blk0 + B_s - 1 of it.
 template <typename R, int MB, int FT>
 __device__ void stage_tile(const DevScene &sc, const RadarConst &rc, const EchoShape &sh,
                            const EchoSmem<R, MB, FT> &sm, const EchoTile<R, MB, FT> &tl, int n,
-                           int32_t cnt, int32_t t0, int nf, int m_tile0, int st) {
+                           int32_t cnt, int32_t t0, int nf, int m_tile0, int blk0, int st) {
   using C = typename Cx<R>::T;
   const int P = rc.P, E = sh.E;
+  const int m_s = sh.B_s * MB, j_first = blk0 * MB;
   const double slope = rc.slope;
   // Each staging wave takes half of the tile's entries through all three steps, so the
   // geometry it reads back was written by itself and needs no workgroup barrier.
@@ -139,13 +148,13 @@ __device__ void stage_tile(const DevScene &sc, const RadarConst &rc, const EchoS
   for (int task = lane; task < kHalf * E; task += 64) {
     const int i = i0 + task / E, e = task % E;
     const Geo g = lds_copy(geo[i]);  // one batch of LDS reads
-    // block-major [B_w][FT][E]: the lanes of a wave (consecutive channels) then read
+    // block-major [B_s][FT][E]: the lanes of a wave (consecutive channels) then read
     // consecutive Rx elements of one block
     C *Ue = tl.U + i * E + e;
     C *re = tl.rat + i * E + e;
     const int bstride = FT * E;
     if (!g.valid) {
-      for (int bb = 0; bb < sh.B_w; ++bb) {
+      for (int bb = 0; bb < sh.B_s; ++bb) {
         Ue[bb * bstride] = {R(0), R(0)};
         re[bb * bstride] = {R(1), R(0)};
       }
@@ -174,16 +183,16 @@ __device__ void stage_tile(const DevScene &sc, const RadarConst &rc, const EchoS
       inv_r = 1.0 / Rn;
     if (!rc.intra) {
       const C step = phasor_m2pi<R>(delta, R(1));
-      for (int bb = 0; bb < sh.B_w; ++bb) {
-        const double m0 = static_cast<double>(m_tile0 + bb * MB);
+      for (int bb = 0; bb < sh.B_s; ++bb) {
+        const double m0 = static_cast<double>(m_tile0 + (blk0 + bb) * MB);
         Ue[bb * bstride] = phasor_m2pi<R>(psi0 + m0 * delta, inv_r);
         re[bb * bstride] = step;
       }
     } else {
       // delay at each sample time t_n + m / fs: exact FP64 phases at both ends of each
       // block; the block runs along their chord (the curvature goes into G)
-      for (int bb = 0; bb < sh.B_w; ++bb) {
-        const int ma = m_tile0 + bb * MB;
+      for (int bb = 0; bb < sh.B_s; ++bb) {
+        const int ma = m_tile0 + (blk0 + bb) * MB;
         const double pa = element_phase(g, rc, sm.elem + 3 * e, e < P, ma);
         const double pb = element_phase(g, rc, sm.elem + 3 * e, e < P, ma + MB);
         Ue[bb * bstride] = phasor_m2pi<R>(pa - floor(pa), inv_r);
@@ -192,9 +201,11 @@ __device__ void stage_tile(const DevScene &sc, const RadarConst &rc, const EchoS
     }
     tl.off[i * E + e] = static_cast<R>(offv);
   }
-  // B2: G_f(m) for the tile's samples, one entry at a time: its record is read from LDS
-  // into registers once (in one batch), not field by field inside the branches
-  for (int ii = 0; ii < kHalf; ++ii) {
+  // B2: G_f(m) for the samples, one entry at a time: its record is read from LDS into
+  // registers once (in one batch), not field by field inside the branches. With fewer samples
+  // than lanes the lanes take several entries at once.
+  const int per = min(64, m_s), at_once = 64 / per;
+  for (int ii = lane / per; ii < kHalf; ii += at_once) {
     const int i = i0 + ii;
     GLin q{};
     Geo g{};
@@ -202,10 +213,10 @@ __device__ void stage_tile(const DevScene &sc, const RadarConst &rc, const EchoS
       q = lds_copy(glin[i]);
     else
       g = lds_copy(geo[i]);
-    for (int j = lane; j < sh.M_t; j += 64) {
+    for (int j = lane % per; j < m_s; j += per) {
       C val = {R(0), R(0)};
       if constexpr (EchoLayout<R, MB, FT>::kRotated) {
-        val = g_lin(q, j);
+        val = g_lin(q, j_first + j);
         if (rc.intra) {
           // deviation of the phase from its chord over the block:
           // exp(-j 2 pi q jj (jj - MB)) to first order (|2 pi q jj (jj - MB)| <= ~2e-4 rad)
@@ -215,14 +226,14 @@ __device__ void stage_tile(const DevScene &sc, const RadarConst &rc, const EchoS
         }
       } else {
         if (g.valid) {
-          const double fm = rc.f0 + static_cast<double>(m_tile0 + j) * rc.df;
+          const double fm = rc.f0 + static_cast<double>(m_tile0 + j_first + j) * rc.df;
           const double s = fm / kC0;  // turns per metre
           const C ph = phi_turns<R>(s * g.beta[0], s * g.beta[1], s * g.beta[2]);
           const R ar = static_cast<R>(g.amp_re), ai = static_cast<R>(g.amp_im);
           val = {ar * ph.x - ai * ph.y, ar * ph.y + ai * ph.x};
         }
       }
-      tl.G[i * sh.M_t + j] = val;
+      tl.G[i * m_s + j] = val;
       if constexpr (EchoLayout<R, MB, FT>::kRotated) {
         // (-j)^(j mod 4): block starts are multiples of 4 samples
         C v1;
@@ -232,20 +243,21 @@ __device__ void stage_tile(const DevScene &sc, const RadarConst &rc, const EchoS
           case 2: v1 = {-val.x, -val.y}; break;
           default: v1 = {-val.y, val.x}; break;
         }
-        tl.G1[i * sh.M_t + j] = v1;
+        tl.G1[i * m_s + j] = v1;
       }
     }
   }
 }
 
-// Accumulation of one staged tile of nf entries into a thread's MB samples. Per sample:
-// one complex multiply-accumulate (4 FMA) and one phasor step. G is read from LDS in
-// blocks of 8 samples, double-buffered in registers; the next facet's element phasors
-// are prefetched.
-template <typename R, int MB, int FT>
+// Accumulation of one staged tile of nf entries into a thread's CH samples, chunk c of block
+// b. Per sample: one complex multiply-accumulate (4 FMA) and one phasor step; a later chunk
+// takes the steps of the chunks before it first (the same steps, so the same phasors,
+// whatever CH). G is read from LDS in blocks of 8 samples, double-buffered in registers; the
+// next facet's element phasors are prefetched.
+template <typename R, int MB, int FT, int CH>
 __device__ inline void sum_tile(const RadarConst &rc, const EchoShape &sh,
-                                const EchoTile<R, MB, FT> &tl, int nf, int p, int q, int b,
-                                typename Cx<R>::T (&acc)[MB]) {
+                                const EchoTile<R, MB, FT> &tl, int nf, int p, int q, int b, int c,
+                                typename Cx<R>::T (&acc)[CH]) {
   using C = typename Cx<R>::T;
   const int P = rc.P, E = sh.E;
   const int iu_p = b * FT * E + p, iu_q = b * FT * E + P + q;
@@ -289,14 +301,32 @@ __device__ inline void sum_tile(const RadarConst &rc, const EchoShape &sh,
       op = tl.off[(i + 1) * E + p];
       oq = tl.off[(i + 1) * E + P + q];
     }
-    const C *Gi = (quarter ? tl.G1 : tl.G) + i * sh.M_t + b * MB;
-    constexpr int kBlk = (MB < 8) ? MB : 8;
+    const C *Gi = (quarter ? tl.G1 : tl.G) + (i * sh.B_s + b) * MB + c * CH;
+    constexpr int kBlk = (CH < 8) ? CH : 8;
     C ga[kBlk], gb[kBlk];
 #pragma unroll
     for (int j = 0; j < kBlk; ++j) ga[j] = Gi[j];
+    // one phasor step
+    const auto step = [&]() __attribute__((always_inline)) {
+      if constexpr (sizeof(R) == 4) {
+        const C zz = {fma_r(c2, zn.x, -z.x), fma_r(c2, zn.y, -z.y)};
+        z = zn;
+        zn = zz;
+      } else {
+        const R zx = fma_r(z.x, r.x, -z.y * r.y);
+        z.y = fma_r(z.x, r.y, z.y * r.x);
+        z.x = zx;
+      }
+    };
+    if constexpr (CH < MB) {
+      for (int k = 0; k < c; ++k) {
 #pragma unroll
-    for (int j0 = 0; j0 < MB; j0 += kBlk) {
-      if (j0 + kBlk < MB) {
+        for (int j = 0; j < CH; ++j) step();
+      }
+    }
+#pragma unroll
+    for (int j0 = 0; j0 < CH; j0 += kBlk) {
+      if (j0 + kBlk < CH) {
 #pragma unroll
         for (int j = 0; j < kBlk; ++j) gb[j] = Gi[j0 + kBlk + j];
       }
@@ -308,15 +338,7 @@ __device__ inline void sum_tile(const RadarConst &rc, const EchoShape &sh,
         a.x = fma_r(-g.y, z.y, a.x);
         a.y = fma_r(g.x, z.y, a.y);
         a.y = fma_r(g.y, z.x, a.y);
-        if constexpr (sizeof(R) == 4) {
-          const C zz = {fma_r(c2, zn.x, -z.x), fma_r(c2, zn.y, -z.y)};
-          z = zn;
-          zn = zz;
-        } else {
-          const R zx = fma_r(z.x, r.x, -z.y * r.y);
-          z.y = fma_r(z.x, r.y, z.y * r.x);
-          z.x = zx;
-        }
+        step();
       }
 #pragma unroll
       for (int j = 0; j < kBlk; ++j) ga[j] = gb[j];
@@ -354,14 +376,14 @@ __device__ inline void store_chunk(const RadarConst &rc, const EchoShape &sh,
   }
 }
 
-// One work item (chirp n, sample tile mt, channel tile ot), split in its two roles. The
-// staging waves and the accumulating waves pass the same barriers: one per tile, then
-// two per output chunk.
-template <typename R, int MB, int FT>
+// One work item (chirp n, sample tile mt, its blocks from blk0 on, channel tile ot), split in
+// its two roles. The staging waves and the accumulating waves pass the same barriers: one per
+// tile, then two per output chunk.
+template <typename R, int MB, int FT, int CH>
 __device__ void echo_stage_item(const DevScene &sc, const RadarConst &rc, const EchoShape &sh,
-                                EchoSmem<R, MB, FT> &sm, int n, int mt, int ot, int st) {
+                                EchoSmem<R, MB, FT> &sm, int n, int mt, int blk0, int ot, int st) {
   using C = typename Cx<R>::T;
-  constexpr int kOut = (MB < 16) ? MB : 16;
+  constexpr int kOut = (CH < 16) ? CH : 16;
   const int m_tile0 = mt * sh.M_t;
   const int32_t cnt = sc.vis_cnt[n];
   const int32_t total = cnt + sc.n_points;
@@ -369,29 +391,29 @@ __device__ void echo_stage_item(const DevScene &sc, const RadarConst &rc, const 
   const C *stage = sm.tile(0).G;  // output staging: the layout reserves O_w x kOut values here
   C *echo_out = static_cast<C *>(sc.echo);
   if (n_tiles > 0)
-    stage_tile<R, MB, FT>(sc, rc, sh, sm, sm.tile(0), n, cnt, 0, min(FT, total), m_tile0, st);
+    stage_tile<R, MB, FT>(sc, rc, sh, sm, sm.tile(0), n, cnt, 0, min(FT, total), m_tile0, blk0, st);
   for (int32_t k = 0; k < n_tiles; ++k) {
     // tile k is staged in buffer k & 1; buffer (k + 1) & 1 was consumed in step k - 1
     __syncthreads();
     const int32_t t1 = (k + 1) * FT;
     if (t1 < total)
       stage_tile<R, MB, FT>(sc, rc, sh, sm, sm.tile((k & 1) ^ 1), n, cnt, t1,
-                            min(FT, total - t1), m_tile0, st);
+                            min(FT, total - t1), m_tile0, blk0, st);
   }
-  for (int bb = 0; bb < sh.B_w; ++bb) {
+  for (int bb = 0; bb < sh.B_s; ++bb) {
     for (int jc = 0; jc < MB; jc += kOut) {
       __syncthreads();
       __syncthreads();
-      store_chunk<R, MB>(rc, sh, stage, echo_out, n, ot, m_tile0 + bb * MB + jc);
+      store_chunk<R, CH>(rc, sh, stage, echo_out, n, ot, m_tile0 + (blk0 + bb) * MB + jc);
     }
   }
 }
 
-template <typename R, int MB, int FT>
+template <typename R, int MB, int FT, int CH>
 __device__ void echo_compute_item(const DevScene &sc, const RadarConst &rc, const EchoShape &sh,
-                                  EchoSmem<R, MB, FT> &sm, int n, int mt, int ot) {
+                                  EchoSmem<R, MB, FT> &sm, int n, int mt, int blk0, int ot) {
   using C = typename Cx<R>::T;
-  constexpr int kOut = (MB < 16) ? MB : 16;
+  constexpr int kOut = (CH < 16) ? CH : 16, kChunks = MB / CH;
   const int tid = threadIdx.x;
   const int m_tile0 = mt * sh.M_t;
   const int32_t total = sc.vis_cnt[n] + sc.n_points;
@@ -400,33 +422,38 @@ __device__ void echo_compute_item(const DevScene &sc, const RadarConst &rc, cons
   C *echo_out = static_cast<C *>(sc.echo);
   const int Q = rc.Q;
   const int ol = tid % sh.O_w;
-  const int b = tid / sh.O_w;
+  const int b = tid / sh.O_w / kChunks, c = tid / sh.O_w % kChunks;
   const int o = ot * sh.O_w + ol;
-  const bool o_ok = b < sh.B_w && o < sh.O;
+  const bool o_ok = b < sh.B_s && o < sh.O;
   const int p = o_ok ? o / Q : 0;
   const int q = o_ok ? o % Q : 0;
-  C acc[MB];
+  C acc[CH];
 #pragma unroll
-  for (int j = 0; j < MB; ++j) acc[j] = {R(0), R(0)};
+  for (int j = 0; j < CH; ++j) acc[j] = {R(0), R(0)};
   for (int32_t k = 0; k < n_tiles; ++k) {
     __syncthreads();
-    if (o_ok) sum_tile<R, MB, FT>(rc, sh, sm.tile(k & 1), min(FT, total - k * FT), p, q, b, acc);
+    if (o_ok)
+      sum_tile<R, MB, FT, CH>(rc, sh, sm.tile(k & 1), min(FT, total - k * FT), p, q, b, c, acc);
   }
-  for (int bb = 0; bb < sh.B_w; ++bb) {
+  for (int bb = 0; bb < sh.B_s; ++bb) {
+    for (int cc = 0; cc < kChunks; ++cc) {
 #pragma unroll
-    for (int jc = 0; jc < MB; jc += kOut) {
-      __syncthreads();
-      if (b == bb) {
+      for (int jc = 0; jc < CH; jc += kOut) {
+        __syncthreads();
+        if (b == bb && c == cc) {
 #pragma unroll
-        for (int j = 0; j < kOut; ++j) stage[ol * kOut + j] = acc[jc + j];
+          for (int j = 0; j < kOut; ++j) stage[ol * kOut + j] = acc[jc + j];
+        }
+        __syncthreads();
+        store_chunk<R, CH>(rc, sh, stage, echo_out, n, ot,
+                           m_tile0 + (blk0 + bb) * MB + cc * CH + jc);
       }
-      __syncthreads();
-      store_chunk<R, MB>(rc, sh, stage, echo_out, n, ot, m_tile0 + bb * MB + jc);
     }
   }
 }
 
-template <typename R, int MB, int FT>
+// One workgroup per (chirp, sample tile, B_s of its blocks, channel tile).
+template <typename R, int MB, int FT, int CH>
 __global__ void __launch_bounds__(512) echo_kernel(DevScene sc, RadarConst rc, const double *elem,
                                                    EchoShape sh) {
   extern __shared__ __align__(16) unsigned char echo_smem[];
@@ -434,14 +461,17 @@ __global__ void __launch_bounds__(512) echo_kernel(DevScene sc, RadarConst rc, c
   sm.carve(echo_smem, sh);
   for (int i = threadIdx.x; i < 3 * sh.E; i += blockDim.x) sm.elem[i] = elem[i];
   __syncthreads();
-  const int per_chirp = sh.m_tiles * sh.o_tiles;
+  const int parts = (sh.B_w + sh.B_s - 1) / sh.B_s;
+  const int per_chirp = sh.m_tiles * parts * sh.o_tiles;
   const int n = blockIdx.x / per_chirp;
   const int r = blockIdx.x % per_chirp;
+  const int ot = r % sh.o_tiles, mt = r / sh.o_tiles / parts;
+  const int blk0 = r / sh.o_tiles % parts * sh.B_s;
+  if (mt * sh.M_t + blk0 * MB >= rc.M) return;  // whole workgroup: past the last sample
   if (threadIdx.x >= sh.n_compute)
-    echo_stage_item<R, MB, FT>(sc, rc, sh, sm, n, r / sh.o_tiles, r % sh.o_tiles,
-                               threadIdx.x - sh.n_compute);
+    echo_stage_item<R, MB, FT, CH>(sc, rc, sh, sm, n, mt, blk0, ot, threadIdx.x - sh.n_compute);
   else
-    echo_compute_item<R, MB, FT>(sc, rc, sh, sm, n, r / sh.o_tiles, r % sh.o_tiles);
+    echo_compute_item<R, MB, FT, CH>(sc, rc, sh, sm, n, mt, blk0, ot);
 }
 
 // Persistent form: a grid sized to the machine drains a queue of work items
@@ -467,7 +497,7 @@ __global__ void __launch_bounds__(512) echo_persistent_kernel(const DevScene *sc
       const int32_t it = __builtin_amdgcn_readfirstlane(s_item);
       if (it >= n_items) break;  // every workgroup reaches this once the queue is drained
       const int4 w = items[it];
-      echo_stage_item<R, MB, FT>(scenes[w.x], rc, sh, sm, w.y, w.z, w.w, st);
+      echo_stage_item<R, MB, FT, MB>(scenes[w.x], rc, sh, sm, w.y, w.z, 0, w.w, st);
     }
   } else {
     while (true) {
@@ -476,7 +506,7 @@ __global__ void __launch_bounds__(512) echo_persistent_kernel(const DevScene *sc
       const int32_t it = __builtin_amdgcn_readfirstlane(s_item);
       if (it >= n_items) break;
       const int4 w = items[it];
-      echo_compute_item<R, MB, FT>(scenes[w.x], rc, sh, sm, w.y, w.z, w.w);
+      echo_compute_item<R, MB, FT, MB>(scenes[w.x], rc, sh, sm, w.y, w.z, 0, w.w);
     }
   }
 }
@@ -496,13 +526,15 @@ struct EchoLaunch {
   int mb, ft;
 };
 
-template <typename R, int MB, int FT>
+template <typename R, int MB, int FT, int CH>
 static hipError_t launch_plain_t(const DevScene &sc, const RadarConst &rc, const double *elem,
                                  const EchoShape &sh, hipStream_t s) {
   const size_t lds = smem_bytes<R, MB, FT>(sh);
   const int threads = sh.n_compute + kStagingThreads;
-  const unsigned grid = static_cast<unsigned>(rc.N) * sh.m_tiles * sh.o_tiles;
-  hipLaunchKernelGGL((echo_kernel<R, MB, FT>), dim3(grid), dim3(threads), lds, s, sc, rc, elem, sh);
+  const unsigned grid = static_cast<unsigned>(rc.N) * sh.m_tiles * sh.o_tiles *
+                        ((sh.B_w + sh.B_s - 1) / sh.B_s);
+  hipLaunchKernelGGL((echo_kernel<R, MB, FT, CH>), dim3(grid), dim3(threads), lds, s, sc, rc, elem,
+                     sh);
   return hipGetLastError();
 }
 
@@ -534,14 +566,28 @@ static hipError_t occupancy_t(const EchoShape &sh, int *groups_per_cu) {
   X(float, 64, 16)            \
   X(double, 8, 8)             \
   X(double, 16, 8)
+// the cut forms: tiles and samples a thread (FP64 with tiles of 16 facets: two staging waves
+// fill one in the time a few short chains take to sum it)
+#define RSIM_ECHO_CUTS(X) \
+  X(float, 64, 16, 16)    \
+  X(float, 64, 16, 32)    \
+  X(double, 16, 16, 8)
 
 #define RSIM_PREC_OF(R) (sizeof(R) == 8 ? 1 : 0)
 
 hipError_t launch_echo_plain(int precision, int mb, int ft, const DevScene &sc, const RadarConst &rc,
                              const double *elem, const EchoShape &sh, hipStream_t s) {
+  if (sh.chunk) {
+#define X(R, MB, FT, CH)                                                             \
+  if (precision == RSIM_PREC_OF(R) && mb == MB && ft == FT && sh.chunk == CH)        \
+    return launch_plain_t<R, MB, FT, CH>(sc, rc, elem, sh, s);
+    RSIM_ECHO_CUTS(X)
+#undef X
+    return hipErrorInvalidValue;
+  }
 #define X(R, MB, FT)                                              \
   if (precision == RSIM_PREC_OF(R) && mb == MB && ft == FT)       \
-    return launch_plain_t<R, MB, FT>(sc, rc, elem, sh, s);
+    return launch_plain_t<R, MB, FT, MB>(sc, rc, elem, sh, s);
   RSIM_ECHO_VARIANTS(X)
 #undef X
   return hipErrorInvalidValue;
@@ -581,6 +627,12 @@ size_t echo_smem_bytes(int precision, int mb, int ft, const EchoShape &sh) {
 #define X(R, MB, FT) \
   if (precision == RSIM_PREC_OF(R) && mb == MB && ft == FT) return smem_bytes<R, MB, FT>(sh);
   RSIM_ECHO_VARIANTS(X)
+#undef X
+#define X(R, MB, FT, CH) \
+  if (precision == RSIM_PREC_OF(R) && mb == MB && ft == FT) return smem_bytes<R, MB, FT>(sh);
+  if (sh.chunk) {
+    RSIM_ECHO_CUTS(X)
+  }
 #undef X
   return 0;
 }

@@ -17,6 +17,9 @@ struct EchoShape {
   int32_t O, O_w, o_tiles, B_w, M_t, m_tiles, E, n_compute;
   double two_pi_slope;  // 2 pi mu
   int32_t accumulate;   // 0: write the echo; 1: add gamma x (this path's echo) to it
+  // forward kernel: blocks of the sample tile a workgroup takes (B_w, or 1 in the cut
+  // forms), and samples a thread takes in those (0: a whole block)
+  int32_t B_s, chunk;
   int32_t pad;
   double gamma_re, gamma_im;
   int32_t slots_tx, slots;  // matrix-core sum: element slots per facet (Tx first, padded)
