@@ -49,9 +49,11 @@ class RadarRDM(torch.autograd.Function):
         ctx.n_inst = len(pos0)
         ctx.intra_chirp = sim.intra_chirp
         # the backward recomputes the chirps from the library's scene, which a later
-        # forward on the same simulator may have replaced: keep this call's geometry
+        # forward on the same simulator may have replaced: keep this call's geometry, to be
+        # loaded again where any vertices or motion were set since
         ctx.verts_np = verts_np
         ctx.vel_np = vel_np
+        ctx.geometry = sim.ctx.geometry_changes
         ctx.save_for_backward(mask, y)
         return rdm[0]
 
@@ -71,7 +73,10 @@ class RadarRDM(torch.autograd.Function):
             per_id[mid] = t
             grads.append(t)
         grad_vel = torch.zeros((ctx.n_inst, 3), dtype=torch.float64, device=dev)
-        RadarRDM._load_geometry(sim, ctx.scene_index, ctx.verts_np, ctx.vel_np)
+        if sim.ctx.geometry_changes != ctx.geometry:
+            RadarRDM._load_geometry(sim, ctx.scene_index, ctx.verts_np, ctx.vel_np)
+        else:
+            torch.cuda.synchronize(dev)  # as loading does: one set of work buffers, any stream
         sim.ctx.set_backward_intra_chirp(ctx.intra_chirp)
         sim.ctx.backward(sim.scene_ids[ctx.scene_index], grad_echo, mask, per_id, grad_vel)
         grads = [g.to(d) for g, d in zip(grads, ctx.vert_devices)]

@@ -876,7 +876,7 @@ int32_t index_mesh(rsim_ctx *ctx, MeshRec &m, bool first_time) {
     }
     first = false;
   }
-  m.r_max = 0.0;
+  double d_max = 0.0;
   for (int64_t t = 0; t < n_tris; ++t) {
     double x[3][3], c[3] = {0.0, 0.0, 0.0};
     for (int v = 0; v < 3; ++v)
@@ -887,9 +887,10 @@ int32_t index_mesh(rsim_ctx *ctx, MeshRec &m, bool first_time) {
     for (int v = 0; v < 3; ++v) {
       double d = 0.0;
       for (int k = 0; k < 3; ++k) d += (x[v][k] - c[k]) * (x[v][k] - c[k]);
-      m.r_max = std::max(m.r_max, std::sqrt(d));
+      d_max = std::max(d_max, d);
     }
   }
+  m.r_max = std::sqrt(d_max);
   std::vector<BvhNode4> nodes;
   std::vector<float> leaf;
   m.depth = build_bvh(m.verts.data(), m.tris.data(), n_tris, nodes, leaf);

@@ -184,6 +184,7 @@ class Context:
         self.device = device
         self.n_tx = self.n_rx = 0
         self.waveform = None
+        self.geometry_changes = 0  # calls that replaced vertices or motion
 
     def close(self):
         if getattr(self, "_h", None):
@@ -239,11 +240,13 @@ class Context:
 
     def update_mesh(self, mesh: int, verts):
         v = np.ascontiguousarray(verts, dtype=np.float32)
+        self.geometry_changes += 1
         self._check(self._L.rsim_update_mesh(self._h, int(mesh), v.ctypes.data, v.shape[0]))
 
     def set_instance_motion(self, scene: int, inst: int, pos0, vel):
         p = np.ascontiguousarray(pos0, np.float64).reshape(3)
         v = np.ascontiguousarray(vel, np.float64).reshape(3)
+        self.geometry_changes += 1
         self._check(self._L.rsim_set_instance_motion(self._h, int(scene), int(inst), _dptr(p),
                                                      _dptr(v)))
 
