@@ -84,9 +84,9 @@ __device__ __forceinline__ void even2_cells(float2 (&acc)[kNuSlots], float2 c0, 
 // guarantee inside the window; those are dropped (their Gaussian weights are below
 // psi(W/2) for every channel). The blocks sit behind independent scalar bit tests rather
 // than a switch: every block then updates the window registers in place, where the merge
-// of a switch's cases costs register copies of the untouched cells. The tests come in two
-// levels, groups of four blocks first: a test that fails is a taken branch, and 23 of them
-// a source left the waves waiting for their instructions.
+// of a switch's cases costs register copies of the untouched cells. The tests come in four
+// levels (halves, quarters, eighths, blocks): a test that fails is a taken branch, and 23 of
+// them a source left the waves waiting for their instructions.
 constexpr int kNuTopStart = 22;  // the last block start
 template <int NCELL, int S0, typename F>
 __device__ __forceinline__ void try_block(uint32_t bit, F &&f) {
@@ -97,16 +97,24 @@ __device__ __forceinline__ void try_block(uint32_t bit, F &&f) {
 template <int NCELL, typename F>
 __device__ __forceinline__ void select_block(int s_lo, F &&f) {
   const uint32_t bit = 1u << s_lo;
-#define RSIM_NU_GROUP(G)                          \
-  if (bit & (0xFu << (4 * G))) {                  \
-    try_block<NCELL, 4 * G>(bit, f);              \
-    try_block<NCELL, 4 * G + 1>(bit, f);          \
-    try_block<NCELL, 4 * G + 2>(bit, f);          \
-    try_block<NCELL, 4 * G + 3>(bit, f);          \
+#define RSIM_NU_3(S)                             \
+  if (bit & (7u << (S))) {                       \
+    try_block<NCELL, (S)>(bit, f);               \
+    try_block<NCELL, (S) + 1>(bit, f);           \
+    try_block<NCELL, (S) + 2>(bit, f);           \
   }
-  RSIM_NU_GROUP(0) RSIM_NU_GROUP(1) RSIM_NU_GROUP(2) RSIM_NU_GROUP(3) RSIM_NU_GROUP(4)
-  RSIM_NU_GROUP(5)
-#undef RSIM_NU_GROUP
+#define RSIM_NU_6(S)                             \
+  if (bit & (0x3Fu << (S))) {                    \
+    RSIM_NU_3(S) RSIM_NU_3((S) + 3)              \
+  }
+#define RSIM_NU_12(S)                            \
+  if (bit & (0xFFFu << (S))) {                   \
+    RSIM_NU_6(S) RSIM_NU_6((S) + 6)              \
+  }
+  RSIM_NU_12(0) RSIM_NU_12(12)
+#undef RSIM_NU_3
+#undef RSIM_NU_6
+#undef RSIM_NU_12
   static_assert(kNuTopStart < 24, "every start has a block");
 }
 
@@ -203,7 +211,9 @@ struct ElemTerm {
 // Bound by the waves' latencies (LDS and scalar loads, transcendentals, the blocks' branches)
 // at the five waves per SIMD that 96 registers leave, the window taking 64 of them; four
 // waves: 95.5 against 88.3 ms. On the 1M-triangle intersection (82M records, 192 channels) the
-// element terms and the two-level block tests took it from 102.8 to 88.3 ms.
+// element terms and block tests in levels took it from 102.8 to 88.3 ms, the head's load after the
+// record's LDS reads to 81.7: 244 VALU instructions a record and wave, of which 162 are the
+// cells', at 3.4 cycles each where 2.4 is the least measured (more for exponentials and FP64).
 template <bool INTRA, int NCELL>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(INTRA ? 4 : 5, 8)))
 nufft_spread_kernel(
@@ -321,10 +331,8 @@ nufft_spread_kernel(
     NuHead nxt = head(0);
     for (int i = 0; i < nb; ++i) {
       const NuHead r = nxt;
-      nxt = head(i + 1 < nb ? i + 1 : i);
       const ElemTerm T = tp[i * E], R = tq[i * E];
       const uint32_t starts = __builtin_amdgcn_readfirstlane(starts_of[i]);
-      if (r.kind == 0) continue;  // wave-uniform
       // this channel's path difference dL = -(s_t + s_r) + e_t + e_r, amplitude, phase and
       // grid position
       const float rel_c = static_cast<float>(r.cell - rr.z) + r.frac;
@@ -348,6 +356,12 @@ nufft_spread_kernel(
       t -= rintf(t);
       const float amp = __builtin_amdgcn_rcpf((r.rt + T.dR) * (r.rr + R.dR));
       const float qx = __builtin_amdgcn_cosf(t) * amp, qy = -__builtin_amdgcn_sinf(t) * amp;
+      // The next head is asked for when this record's LDS reads are in: one counter holds both
+      // kinds of load, so a wait for the LDS would wait for the head, too.
+      __builtin_amdgcn_sched_barrier(0);
+      nxt = head(i + 1 < nb ? i + 1 : i);
+      __builtin_amdgcn_sched_barrier(0);
+      // no source for a record of kind 0 (a branch around the work here costs register copies)
       const int n_pts = r.kind == 1 ? 3 : r.kind == 2 ? 1 : 0;
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
