@@ -650,14 +650,14 @@ const char *nufft_common(const rsim_ctx *ctx, const RadarConst &rc, const rsim_o
   return nullptr;
 }
 
-// Channels per FFT workgroup: two workgroups per CU where the LDS allows (extra_lds:
+// Channels per FFT workgroup: four workgroups per CU where the LDS allows (extra_lds:
 // bytes beyond the two row buffers).
 void nufft_fft_groups(const rsim_ctx *ctx, const RadarConst &rc, NuShape &s, size_t extra_lds) {
   s.cb = 0;
   for (int cb = 16; cb >= 1 && !s.cb; --cb) {
     NuShape t = s;
     t.cb = cb;
-    if (nufft_smem_bytes(t) + extra_lds <= ctx->max_lds / 2) s.cb = cb;
+    if (nufft_smem_bytes(t) + extra_lds <= ctx->max_lds / 4) s.cb = cb;
   }
   if (!s.cb) s.cb = 1;
   const int O = rc.P * rc.Q;

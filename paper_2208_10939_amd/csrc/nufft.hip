@@ -76,7 +76,7 @@ constexpr int kNuMaxOrder = 4;  // Hermite table rows (three Taylor terms are us
 constexpr int kNuSortThreads = 1024;  // 16 waves: each ranks one sixteenth of a chirp's entries
 constexpr int kNuSortWaves = kNuSortThreads / 64;
 constexpr int kNuGatherRecs = 256;  // records (lanes) per adjoint gather workgroup
-constexpr int kNuRedBatch = 8;      // run windows read together by a cell sum of the FFT kernel
+constexpr int kNuRedBatch = 16;     // run windows read together by a cell sum of the FFT kernel
 constexpr int kNuGatherStage = 4096;  // grid cells staged in LDS by a gather workgroup (32 KB)
 static_assert(kNuGatherStage >= 2048 + 12, "a whole row fits the gather's staging");
 constexpr int kXcds = 8;            // accelerator complex dies: workgroups go round-robin
@@ -756,7 +756,10 @@ __device__ inline int lower_bound_lds(const int32_t *bases, int n, int v) {
 // Per (chirp, group of cb channels): each grid cell l summed from the run windows that
 // cover it (at l, l - n_g or l + n_g on the periodic grid; in order of the runs' base
 // cells, which is the run order), forward FFT of all cb rows together (ping-pong buffers),
-// deconvolution and the k_c^2 / k_m^2 factor on the M kept modes.
+// deconvolution and the k_c^2 / k_m^2 factor on the M kept modes. Bound by the windows' way from
+// memory (50k facets, 64 chirps: 1.4 GB), so by the loads in flight: 16 a thread and groups of a
+// quarter of a CU's LDS, four to a CU, take 326 us where 8 and halves took 498 (16 and halves
+// 401, 8 and quarters 376, 16 and eighths 409).
 __global__ void __launch_bounds__(kNuFftThreads) nufft_fft_kernel(DevScene sc0, RadarConst rc,
                                                                 NuShape ns, NuBuffers nb,
                                                                 const float2 *tw, NuBatch bt) {
