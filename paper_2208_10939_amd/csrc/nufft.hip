@@ -1262,6 +1262,10 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 // Class 0: three points (kind 1); class 1: a point (zero weight for kind 3) and a
 // quadratic. Blocks are ordered so that those of one chirp share an XCD (and its L2, which
 // holds the chirp's grids).
+// Bound by instruction issue (470 a channel before, 273 of them the moments', at 2.9 cycles each
+// and three waves a SIMD): the elements' offsets in LDS and a Tx element's terms kept for its
+// channels leave four waves, 4.34 -> 3.98 ms (120k facets, 40 chirps, 192 channels). The
+// roundings are those of a channel's own terms, spelled out.
 template <int CLS>
 __global__ void __launch_bounds__(kNuGatherRecs) nufft_gather_kernel(
     DevScene sc, RadarConst rc, NuShape ns, const double *elem,
@@ -1274,6 +1278,15 @@ __global__ void __launch_bounds__(kNuGatherRecs) nufft_gather_kernel(
                                       // stretch [lo, lo + span) the sources reach
   __shared__ int32_t reach[3];        // lowest and one past the highest cell reached; 1 if
                                       // some bound lies outside [-n_g, 2 n_g]
+  // the elements' offsets from their phase centres, and their squared lengths
+  __shared__ double off[kMaxElements][3];
+  __shared__ float off2[kMaxElements];
+  for (int e = threadIdx.x; e < rc.P + rc.Q; e += blockDim.x) {
+    for (int k = 0; k < 3; ++k) off[e][k] = elem[3 * e + k] - (e < rc.P ? rc.tx_c[k] : rc.rx_c[k]);
+    const double *a = off[e];
+    const double a2 = fma(a[2], a[2], fma(a[0], a[0], a[1] * a[1]));
+    off2[e] = static_cast<float>(a2);
+  }
   const int per_xcd = (gridDim.x + kXcds - 1) / kXcds;  // gridDim.x is a multiple of kXcds
   const int logical = static_cast<int>(blockIdx.x % kXcds) * per_xcd + static_cast<int>(blockIdx.x / kXcds);
   const int nl = logical / blocks_per_chirp;
@@ -1379,6 +1392,28 @@ __global__ void __launch_bounds__(kNuGatherRecs) nufft_gather_kernel(
   const int s_base = wrap ? 0 : (lo % ng + ng) % ng;  // grid cell of the first staged one
   // as many channels' rows per staging (and barrier pair) as kNuGatherStage cells hold
   const int per_stage = max(1, min(O, kNuGatherStage / n_stage));
+  // What the record's channels owe to element e, at unit vector u and distance dist from its
+  // phase centre: u.a, the remainder, the path difference and 1 / distance. A Tx element's is
+  // formed once for its Q channels.
+  struct ElemPath {
+    double s;
+    float q, c, dR, inv_R;  // the remainder is q c
+  };
+  const auto element_term = [&](int e, const double (&u)[3], float dist)
+                                __attribute__((always_inline)) {
+    ElemPath T;
+    T.s = fma(u[2], off[e][2], fma(u[0], off[e][0], u[1] * off[e][1]));
+    const float sf = static_cast<float>(T.s);
+    const float h = fmaf(-sf, sf, off2[e]);
+    const float rd = __builtin_amdgcn_rcpf(fmaf(-2.0f, sf, 2.0f * dist));
+    T.q = h * rd;
+    T.c = fmaf(-T.q, rd, 1.0f);
+    T.dR = fmaf(T.q, T.c, -sf);
+    T.inv_R = __builtin_amdgcn_rcpf(dist + T.dR);
+    return T;
+  };
+  ElemPath tx{};
+  int tx_of = -1;
   for (int o0 = 0; o0 < O; o0 += per_stage) {
   const int nch = min(per_stage, O - o0);
   __syncthreads();  // the previous channels' rows are no longer read
@@ -1392,35 +1427,21 @@ __global__ void __launch_bounds__(kNuGatherRecs) nufft_gather_kernel(
   __syncthreads();
   for (int o = o0; o < o0 + nch; ++o) {
     const float2 *row = nu_row + (o - o0) * n_stage;
-    // this channel's element offsets from the phase centres (wave-uniform)
-    const int p = o / rc.Q, q = o - p * rc.Q;
-    double at[3], ar[3];
-    double st2 = 0.0, sr2 = 0.0;
-    for (int k = 0; k < 3; ++k) {
-      at[k] = elem[3 * p + k] - rc.tx_c[k];
-      ar[k] = elem[3 * (rc.P + q) + k] - rc.rx_c[k];
-      st2 += at[k] * at[k];
-      sr2 += ar[k] * ar[k];
-    }
-    const float aat = static_cast<float>(st2), aar = static_cast<float>(sr2);
     // the channel's path (as in the spread)
-    const double st = r.ut[0] * at[0] + r.ut[1] * at[1] + r.ut[2] * at[2];
-    const double sr = r.ur[0] * ar[0] + r.ur[1] * ar[1] + r.ur[2] * ar[2];
-    const double ps = (st + sr) * r.g1;
-    const float pr = static_cast<float>(ps - rint(ps));
-    const float sft = static_cast<float>(st), sfr = static_cast<float>(sr);
-    const float ht = fmaf(-sft, sft, aat), hr = fmaf(-sfr, sfr, aar);
-    const float rdt = __builtin_amdgcn_rcpf(fmaf(-2.0f, sft, 2.0f * r.rt));
-    const float rdr = __builtin_amdgcn_rcpf(fmaf(-2.0f, sfr, 2.0f * r.rr));
-    const float qt = ht * rdt, qr = hr * rdr;
-    const float et = qt * fmaf(-qt, rdt, 1.0f), er = qr * fmaf(-qr, rdr, 1.0f);
-    const float dRt = et - sft, dRr = er - sfr;
-    const float dL = dRt + dRr;
-    float t = (r.t0 - pr) + fmaf(g1f, et + er, -g2 * dL * dL);
+    const int p = o / rc.Q, q = o - p * rc.Q;
+    const double *at = off[p], *ar = off[rc.P + q];
+    if (p != tx_of) {  // wave-uniform
+      tx = element_term(p, r.ut, r.rt);
+      tx_of = p;
+    }
+    const ElemPath rx = element_term(rc.P + q, r.ur, r.rr);
+    const double path = tx.s + rx.s;
+    const float pr = static_cast<float>(fma(path, r.g1, -rint(path * r.g1)));  // turns
+    const float irt = tx.inv_R, irr = rx.inv_R;
+    const float dL = tx.dR + rx.dR;
+    float t = (r.t0 - pr) + fmaf(g1f, fmaf(tx.q, tx.c, rx.q * rx.c), -g2 * dL * dL);
     t -= rintf(t);
     const float x = fmaf(kappa, dL, r.frac);  // grid position minus the record's cell
-    const float Rtp = r.rt + dRt, Rrq = r.rr + dRr;
-    const float irt = __builtin_amdgcn_rcpf(Rtp), irr = __builtin_amdgcn_rcpf(Rrq);
     const float amp = irt * irr;
     const float2 Q = {__builtin_amdgcn_cosf(t) * amp, -__builtin_amdgcn_sinf(t) * amp};
     // y / Q and (dy/dx) / Q over the sources; per-parameter sums
