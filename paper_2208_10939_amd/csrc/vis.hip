@@ -25,7 +25,6 @@ namespace rsim {
 namespace {
 
 constexpr int kVisThreads = 256;
-constexpr int kVisFilterFacets = 32;  // facets per workgroup with 64 chirps per group
 constexpr int kVisBitWords = 4 * 64;  // LDS bit words: path types x chirps x mask words
 
 __device__ inline int find_instance(const DevInstance *inst, int n_inst, int64_t f) {
@@ -687,22 +686,21 @@ __device__ inline double dot3(const double *a, const double *b) {
   return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
 }
 
-// The pair search's instance filter for facet f (the wave's one facet) at chirps n_a .. n_b:
-// for each launching end k, the instances (bit j for instance j < 64) that the shadow
-// segment c(t) -> E (out[2 k]) or the specular segment c(t) -> c(t) + ray_len r(t)
-// (out[2 k + 1]) of some chirp may meet. Lane j tests instance j with the segments at the
-// middle time against its box swept over the chirps' times and grown: by the centroid's
+// The pair search's instance filter for facet f and instance j at chirps n_a .. n_b: may, for
+// launching end k, the shadow segment c(t) -> E (bit 2 k) or the specular segment c(t) -> c(t) +
+// ray_len r(t) (bit 2 k + 1) of some chirp meet the instance? The segments at the
+// middle time are tested against its box swept over the chirps' times and grown: by the centroid's
 // sweep per axis for the shadow segment (as in visibility); for the specular one by
 // |delta| (1 + 2 ray_len / (|E - c_m| - |delta|)), |delta| the centroid's largest
 // displacement from its middle position (the unit vector towards E turns by at most
 // 2 |delta| / (|E - c_m| - |delta|), and the mirror in A's plane, fixed under translation,
-// keeps that), plus 1e-6 m against rounding. Supersets of what the per-chirp FP64 box
-// tests admit; all instances where that bound does not apply.
-__device__ void db_wave_candidates(const DevScene &sc, const RadarConst &rc, int64_t f, int n_a,
-                                   int n_b, double ray_len, uint64_t out[4]) {
-  const int lane = threadIdx.x & 63;
+// keeps that), plus 1e-6 m against rounding. True wherever the per-chirp FP64 box
+// tests admit the instance, and where that bound does not apply.
+__device__ uint32_t db_candidate(const DevScene &sc, const RadarConst &rc, int64_t f, int j,
+                                 int n_a, int n_b, double ray_len) {
   const double ta = n_a * rc.tc, tb = n_b * rc.tc, tm = 0.5 * (ta + tb);
   const DevInstance &A = sc.inst[find_instance(sc.inst, sc.n_inst, f)];
+  const DevInstance &I = sc.inst[j];
   double x[3][3], c[3], na[3];
   world_vertices(A, f - A.facet_base, tm, x);
   const bool ok = tri_frame(x, c, na);
@@ -713,36 +711,29 @@ __device__ void db_wave_candidates(const DevScene &sc, const RadarConst &rc, int
     sweep += dk * dk;
   }
   sweep = sqrt(sweep);
+  uint32_t may = 0;
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     const double *E = k ? rc.rx_c : rc.tx_c;
     double de[3] = {E[0] - c[0], E[1] - c[1], E[2] - c[2]};
     const double ld = sqrt(dot3(de, de));
-    bool all = !ok || !(ld - sweep > 0.0);
-    double end[3], gr[3];
-    if (!all) {
-      double r[3];
-      for (int q = 0; q < 3; ++q) r[q] = -de[q] / ld;
-      const double rn = dot3(r, na);
-      for (int q = 0; q < 3; ++q) {
-        r[q] -= 2.0 * rn * na[q];
-        end[q] = c[q] + ray_len * r[q];
-      }
-      const double g = sweep * (1.0 + 2.0 * ray_len / (ld - sweep)) + 1e-6;
-      gr[0] = gr[1] = gr[2] = g;
+    if (!ok || !(ld - sweep > 0.0)) {
+      may |= 3u << (2 * k);
+      continue;
     }
-    bool ce = true, cr = true;
-    if (lane < sc.n_inst && !all) {
-      const DevInstance &I = sc.inst[lane];
-      double lo[3], hi[3];
-      swept_box(I, ta, tb, hw, lo, hi);
-      ce = seg_box(c, E, lo, hi);
-      swept_box(I, ta, tb, gr, lo, hi);
-      cr = seg_box(c, end, lo, hi);
-    }
-    out[2 * k] = __ballot(ce);
-    out[2 * k + 1] = __ballot(cr);
+    double r[3], end[3];
+    for (int q = 0; q < 3; ++q) r[q] = -de[q] / ld;
+    const double rn = dot3(r, na);
+    for (int q = 0; q < 3; ++q) end[q] = c[q] + ray_len * (r[q] - 2.0 * rn * na[q]);
+    const double g = sweep * (1.0 + 2.0 * ray_len / (ld - sweep)) + 1e-6;
+    const double gr[3] = {g, g, g};
+    double lo[3], hi[3];
+    swept_box(I, ta, tb, hw, lo, hi);
+    if (seg_box(c, E, lo, hi)) may |= 1u << (2 * k);
+    swept_box(I, ta, tb, gr, lo, hi);
+    if (seg_box(c, end, lo, hi)) may |= 2u << (2 * k);
   }
+  return may;
 }
 
 // Facet B that the ray launched from end k (0: Tx phase centre, 1: Rx) reflected off facet A
@@ -857,40 +848,48 @@ __device__ int32_t db_connect(const DevScene &sc, const RadarConst &rc, int64_t 
 }  // namespace
 
 // Connections of every facet at chirps n_begin .. n_begin + n_chirps - 1, both launching
-// ends: pair_b[(k N + n) F + f]. Workgroups as in vis_kernel (lane = chirp).
-__global__ void __launch_bounds__(kVisThreads) dbounce_kernel(DevScene sc, RadarConst rc, int cw,
+// ends: pair_b[(k N + n) F + f]. Lane = chirp, as in vis_kernel. Bound by the walks of the BVH,
+// each lane its own (the nearest hit depends on the order of a walk where triangles tie): the
+// instance filter for every size, four waves a SIMD and one pass a workgroup took 2.30 -> 1.12
+// ms for 120k facets of 7 instances and 64 chirps, 0.42 -> 0.14 ms for 20k of one.
+__global__ void __launch_bounds__(kVisThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) dbounce_kernel(DevScene sc, RadarConst rc, int cw,
                                                             int facets_per_block, int n_begin,
                                                             int n_end, double ray_len,
                                                             double r_lim, int32_t *pair_b) {
   extern __shared__ int32_t db_lds[];
-  __shared__ uint64_t cand_lds[kVisFilterFacets][4];
-  int32_t *stk = db_lds + threadIdx.x;  // column per thread
+  uint32_t *cand = reinterpret_cast<uint32_t *>(db_lds);             // [facet][segment][2 words]
+  int32_t *stk = db_lds + 8 * facets_per_block + threadIdx.x;  // column per thread
   const int nl = threadIdx.x % cw;
   const int n = n_begin + static_cast<int>(blockIdx.y) * cw + nl;
   const int64_t f0 = static_cast<int64_t>(blockIdx.x) * facets_per_block;
-  // with 64 chirps per group (a wave per facet) each facet's instances are filtered first
-  const bool filter = cw == 64 && facets_per_block <= kVisFilterFacets;
+  // with several instances, those that each facet's segments may meet are found first, a thread
+  // per (facet, instance)
+  const bool filter = sc.n_inst > 1;
+  for (int k = threadIdx.x; k < 8 * facets_per_block; k += blockDim.x) cand[k] = 0u;
+  __syncthreads();
   if (filter) {
     const int n_a = n_begin + static_cast<int>(blockIdx.y) * cw;
     const int n_b = min(n_end, n_a + cw) - 1;
-    for (int fl = threadIdx.x >> 6; fl < facets_per_block; fl += blockDim.x >> 6) {
-      const int64_t f = f0 + fl;
-      if (f >= sc.n_facets) break;  // wave-uniform
-      uint64_t m[4];
-      db_wave_candidates(sc, rc, f, n_a, n_b, ray_len, m);
-      if ((threadIdx.x & 63) == 0)
-        for (int q = 0; q < 4; ++q) cand_lds[fl][q] = m[q];
+    const int ni = min(sc.n_inst, 64);
+    for (int k = threadIdx.x; k < facets_per_block * ni; k += blockDim.x) {
+      const int fl = k / ni, j = k % ni;
+      if (f0 + fl >= sc.n_facets) break;
+      const uint32_t may = db_candidate(sc, rc, f0 + fl, j, n_a, n_b, ray_len);
+      for (int q = 0; q < 4; ++q)
+        if ((may >> q) & 1u) atomicOr(&cand[8 * fl + 2 * q + (j >> 5)], 1u << (j & 31));
     }
     __syncthreads();
   }
+  const auto of = [&](int fl, int q) {
+    const uint32_t *w = cand + 8 * fl + 2 * q;
+    return filter ? static_cast<uint64_t>(w[1]) << 32 | w[0] : ~uint64_t(0);
+  };
   for (int fl = threadIdx.x / cw; fl < facets_per_block; fl += blockDim.x / cw) {
     const int64_t f = f0 + fl;
     if (f >= sc.n_facets || n >= n_end) continue;
     for (int k = 0; k < 2; ++k) {
-      const uint64_t ce = filter ? cand_lds[fl][2 * k] : ~uint64_t(0);
-      const uint64_t cr = filter ? cand_lds[fl][2 * k + 1] : ~uint64_t(0);
       pair_b[(static_cast<int64_t>(k) * rc.N + n) * sc.n_facets + f] =
-          db_connect(sc, rc, f, n, k, ray_len, r_lim, stk, blockDim.x, ce, cr);
+          db_connect(sc, rc, f, n, k, ray_len, r_lim, stk, blockDim.x, of(fl, 2 * k), of(fl, 2 * k + 1));
     }
   }
 }
@@ -933,10 +932,14 @@ hipError_t launch_dbounce(const DevScene &sc, const RadarConst &rc, double ray_l
   if (sc.n_facets > 0 && ray_len > 0.0) {
     int cw = 1;
     while (cw < rc.N && cw < 64) cw <<= 1;
-    const int fpb = std::max(32, kVisThreads / cw);
+    // as in visibility: few facets leave lanes idle rather than waves (20k facets, 4 chirps:
+    // 179 us at cw 4, 129 at 32)
+    while (cw < 32 && sc.n_facets * cw < int64_t{64} * 8192) cw <<= 1;
+    const int fpb = kVisThreads / cw;  // one pass a workgroup: the walks' lengths differ widely
     dim3 grid(static_cast<unsigned>((sc.n_facets + fpb - 1) / fpb),
               static_cast<unsigned>((rc.N + cw - 1) / cw));
-    const size_t lds = sizeof(int32_t) * static_cast<size_t>(sc.stack_depth) * kVisThreads;
+    const size_t lds =
+        sizeof(int32_t) * (8 * fpb + static_cast<size_t>(sc.stack_depth) * kVisThreads);
     hipLaunchKernelGGL(dbounce_kernel, grid, dim3(kVisThreads), lds, s, sc, rc, cw, fpb, 0,
                        rc.N, ray_len, r_lim, pair_b);
     hipError_t e = hipGetLastError();
