@@ -689,7 +689,7 @@ __global__ void __launch_bounds__(kNuSortThreads) nufft_sort_kernel(DevScene sc0
   if (tid == 0) cbase[ng] = n_ent;
   __syncthreads();
   // runs: cut by the first wave over the occupied cells, 64 cells in its lanes at a time (one
-  // lane reading cell after cell from LDS was over half of the kernel: 76 us for 3k facets)
+  // lane reading cell after cell from LDS was over half of the kernel: 76 us for 20k facets, 24 now)
   if (w == 0) {
     int4 *runs = nb.runs + wk.run;
     int nr = 0;
@@ -763,7 +763,7 @@ __device__ inline int lower_bound_lds(const int32_t *bases, int n, int v) {
 // cover it (at l, l - n_g or l + n_g on the periodic grid; in order of the runs' base
 // cells, which is the run order), forward FFT of all cb rows together (ping-pong buffers),
 // deconvolution and the k_c^2 / k_m^2 factor on the M kept modes. Bound by the windows' way from
-// memory (50k facets, 64 chirps: 1.4 GB), so by the loads in flight: 16 a thread and groups of a
+// memory (50k facets, 128 chirps: 1.4 GB), so by the loads in flight: 16 a thread and groups of a
 // quarter of a CU's LDS, four to a CU, take 326 us where 8 and halves took 498 (16 and halves
 // 401, 8 and quarters 376, 16 and eighths 409).
 __global__ void __launch_bounds__(kNuFftThreads) nufft_fft_kernel(DevScene sc0, RadarConst rc,

@@ -13,8 +13,8 @@
 // visibility walks a BVH once a wave: nodes and triangles in scalar registers, a mask of the
 // lanes inside each node, one small stack a wave. Bound by the chain of a wave's node fetches
 // and by its box tests. Against a walk per lane (32 node registers and an LDS stack column a
-// lane, 4 waves a SIMD), 64 chirps: 50k facets 433 -> 190 us, 20k 235 -> 74 us, 50k
-// with ground paths 565 -> 230 us; 1M facets, 128 chirps 15.0 -> 8.8 ms.
+// lane, 4 waves a SIMD): 50k facets x 128 chirps 433 -> 190 us, 30k x 64 235 -> 74 us, 20k x 81
+// with ground paths 565 -> 230 us, 1M x 256 15.0 -> 8.8 ms.
 #include <algorithm>
 
 #include "rsim_internal.h"
@@ -966,13 +966,13 @@ hipError_t launch_visibility(const DevScene &sc, const RadarConst &rc, int n_beg
   int threads = kVisThreads, fpb = 8;
   if (sc.n_facets * ((n_chirps + 63) / 64) <= 8192) {
     // a wave's one chain of nodes is the time: one facet a wave (1k facets, 4 chirps: 24 us; 30
-    // at cw 32 with 256 threads. 20k facets, 64 chirps: 84, 74 with 256)
+    // at cw 32 with 256 threads. 30k facets, 64 chirps: 84, 74 with 256)
     cw = 64;
     threads = 2 * kVisThreads;
   }
   // Facets per workgroup, 8, 16 or whole mask words: small ones even out the waves' work, large
-  // ones share the start of a workgroup (50k facets, 64 chirps: 190 us at 8, 232 at 32; 1M
-  // facets, 128 chirps: 9740 at 8, 8770 at 32)
+  // ones share the start of a workgroup (50k facets, 128 chirps: 190 us at 8, 232 at 32; 1M
+  // facets, 256 chirps: 9740 at 8, 8770 at 32)
   while (fpb < 32 && sc.n_facets * chirp_groups() > int64_t{16384} * fpb) fpb *= 2;
   fpb = std::max(fpb, threads / cw);
   dim3 grid(static_cast<unsigned>((32 * sc.mask_words + fpb - 1) / fpb),
