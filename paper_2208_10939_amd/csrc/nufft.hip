@@ -1262,12 +1262,17 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 // Class 0: three points (kind 1); class 1: a point (zero weight for kind 3) and a
 // quadratic. Blocks are ordered so that those of one chirp share an XCD (and its L2, which
 // holds the chirp's grids).
-// Bound by instruction issue (470 a channel before, 273 of them the moments', at 2.9 cycles each
-// and three waves a SIMD): the elements' offsets in LDS and a Tx element's terms kept for its
-// channels leave four waves, 4.34 -> 3.98 ms (120k facets, 40 chirps, 192 channels). The
+// Bound by instruction issue (273 of 470 a channel were the moments', at 2.9 cycles each) and,
+// where a call has few workgroups, by a channel's chain of latencies. The elements' offsets lie in
+// LDS, the next channel's Rx element's are asked for a channel ahead, and a Tx element's terms
+// are kept for its channels. Three waves a SIMD: with four, which the registers would allow, a call
+// of some 3 workgroups a CU got 4 on some CUs and 2 on others. 192 channels, 48 chirps, kinds 1 (kind
+// 2 and 3), against every channel forming its own terms: 10k facets 434 -> 395 us (260 -> 240), 24k
+// 820 -> 755 (264 -> 243); offsets at four waves and not ahead took 507 (261) and 769 (266). The
 // roundings are those of a channel's own terms, spelled out.
 template <int CLS>
-__global__ void __launch_bounds__(kNuGatherRecs) nufft_gather_kernel(
+__global__ void __launch_bounds__(kNuGatherRecs) __attribute__((amdgpu_waves_per_eu(1, 3)))
+nufft_gather_kernel(
     DevScene sc, RadarConst rc, NuShape ns, const double *elem,
     const NuRecF<false> *__restrict__ recs, const NuDerF *__restrict__ ders,
     const int32_t *__restrict__ lists, const int32_t *__restrict__ counts,
@@ -1399,12 +1404,19 @@ __global__ void __launch_bounds__(kNuGatherRecs) nufft_gather_kernel(
     double s;
     float q, c, dR, inv_R;  // the remainder is q c
   };
-  const auto element_term = [&](int e, const double (&u)[3], float dist)
+  struct ElemOff {
+    double k[3];
+    float sq;
+  };
+  const auto offset_of = [&](int e) {
+    return ElemOff{{off[e][0], off[e][1], off[e][2]}, off2[e]};
+  };
+  const auto element_term = [&](const ElemOff &a, const double (&u)[3], float dist)
                                 __attribute__((always_inline)) {
     ElemPath T;
-    T.s = fma(u[2], off[e][2], fma(u[0], off[e][0], u[1] * off[e][1]));
+    T.s = fma(u[2], a.k[2], fma(u[0], a.k[0], u[1] * a.k[1]));
     const float sf = static_cast<float>(T.s);
-    const float h = fmaf(-sf, sf, off2[e]);
+    const float h = fmaf(-sf, sf, a.sq);
     const float rd = __builtin_amdgcn_rcpf(fmaf(-2.0f, sf, 2.0f * dist));
     T.q = h * rd;
     T.c = fmaf(-T.q, rd, 1.0f);
@@ -1413,7 +1425,9 @@ __global__ void __launch_bounds__(kNuGatherRecs) nufft_gather_kernel(
     return T;
   };
   ElemPath tx{};
+  float at[3] = {};  // its offsets
   int tx_of = -1;
+  ElemOff next_rx = offset_of(rc.P);
   for (int o0 = 0; o0 < O; o0 += per_stage) {
   const int nch = min(per_stage, O - o0);
   __syncthreads();  // the previous channels' rows are no longer read
@@ -1429,12 +1443,16 @@ __global__ void __launch_bounds__(kNuGatherRecs) nufft_gather_kernel(
     const float2 *row = nu_row + (o - o0) * n_stage;
     // the channel's path (as in the spread)
     const int p = o / rc.Q, q = o - p * rc.Q;
-    const double *at = off[p], *ar = off[rc.P + q];
     if (p != tx_of) {  // wave-uniform
-      tx = element_term(p, r.ut, r.rt);
+      const ElemOff a = offset_of(p);
+      tx = element_term(a, r.ut, r.rt);
+      for (int k = 0; k < 3; ++k) at[k] = static_cast<float>(a.k[k]);
       tx_of = p;
     }
-    const ElemPath rx = element_term(rc.P + q, r.ur, r.rr);
+    const ElemPath rx = element_term(next_rx, r.ur, r.rr);
+    const float ar[3] = {static_cast<float>(next_rx.k[0]), static_cast<float>(next_rx.k[1]),
+                         static_cast<float>(next_rx.k[2])};
+    next_rx = offset_of(rc.P + (q + 1 < rc.Q ? q + 1 : 0));
     const double path = tx.s + rx.s;
     const float pr = static_cast<float>(fma(path, r.g1, -rint(path * r.g1)));  // turns
     const float irt = tx.inv_R, irr = rx.inv_R;
@@ -1504,9 +1522,9 @@ __global__ void __launch_bounds__(kNuGatherRecs) nufft_gather_kernel(
     }
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const float ep = (static_cast<float>(at[k]) - r.rt * utf[k]) * irt;
-      const float eq = (static_cast<float>(ar[k]) - r.rr * urf[k]) * irr;
-      acc_c[k] -= ct * ep + cr * eq;
+      const float ep = (at[k] - r.rt * utf[k]) * irt;
+      const float eq = (ar[k] - r.rr * urf[k]) * irr;
+      acc_c[k] -= fmaf(ct, ep, cr * eq);
     }
   }
   }
