@@ -196,15 +196,38 @@ struct ElemTerm {
   double s;
   float e, dR;
 };
+// a: its offset from the phase centre, of squared length a2; u: the unit vector to that centre,
+// `dist` away
+__device__ __forceinline__ ElemTerm element_term(const double *u, float dist, const double (&a)[3],
+                                                 float a2) {
+  const double s = u[0] * a[0] + u[1] * a[1] + u[2] * a[2];
+  const float sf = static_cast<float>(s);
+  const float h = fmaf(-sf, sf, a2);
+  const float rd = __builtin_amdgcn_rcpf(fmaf(-2.0f, sf, 2.0f * dist));
+  const float qd = h * rd;
+  const float ed = qd * fmaf(-qd, rd, 1.0f);
+  return {s, ed, ed - sf};
+}
+// With the delay within the chirp: the rate of the element's distance, v the source's velocity
+// and `rate` that of the centre's distance.
+__device__ __forceinline__ float element_rate(const float *v, float rate, float dist, float dR,
+                                              const double (&a)[3]) {
+  const float af[3] = {static_cast<float>(a[0]), static_cast<float>(a[1]),
+                       static_cast<float>(a[2])};
+  const float va = v[0] * af[0] + v[1] * af[1] + v[2] * af[2];
+  return fmaf(dist, rate, -va) * __builtin_amdgcn_rcpf(dist + dR);
+}
 
 }  // namespace
 
 // One workgroup per (chirp, run) and up to four 64-channel groups (blockIdx.z counts
 // further groups); lane = channel. A run's records are taken batch by batch:
-//  - staging: a lane per (record, element) forms what the record's channels owe to that Tx
+//  - staging (STAGED): a lane per (record, element) forms what the record's channels owe to that Tx
 //    or Rx element, into LDS: P + Q elements for P Q channels (28 for 192 on the 12 x 16
 //    array), where every lane forming its own channel's took a fifth of the kernel's
-//    instructions; then a lane per record the first cells of the record's blocks;
+//    instructions; then a lane per record the first cells of the record's blocks. Arrays with
+//    few channels to an element go without (launch_nufft_spread has the rule): a lane forms its
+//    own two terms from the record in scalar registers;
 //  - spread: per record a lane joins its two elements' terms and adds the record's sources
 //    into its register window of kNuSlots cells, which starts at the run's base cell and
 //    goes to part[chirp][run][channel][kNuSlots] at the run's end.
@@ -214,7 +237,7 @@ struct ElemTerm {
 // element terms and block tests in levels took it from 102.8 to 88.3 ms, the head's load after the
 // record's LDS reads to 81.7: 244 VALU instructions a record and wave, of which 162 are the
 // cells', at 3.4 cycles each where 2.4 is the least measured (more for exponentials and FP64).
-template <bool INTRA, int NCELL>
+template <bool INTRA, int NCELL, bool STAGED>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(INTRA ? 4 : 5, 8)))
 nufft_spread_kernel(
     DevScene sc0, RadarConst rc, NuShape ns, const double *elem,
@@ -230,9 +253,11 @@ nufft_spread_kernel(
   double *off = reinterpret_cast<double *>(term + batch * E);              // [E][3]
   float *rdot = reinterpret_cast<float *>(off + 3 * E);                    // [batch][E] (INTRA)
   int32_t *all_starts = reinterpret_cast<int32_t *>(rdot + (INTRA ? batch * E : 0));
-  for (int i = threadIdx.x; i < 3 * E; i += blockDim.x) {
-    const int k = i % 3;
-    off[i] = elem[i] - (i < 3 * rc.P ? rc.tx_c[k] : rc.rx_c[k]);
+  if constexpr (STAGED) {
+    for (int i = threadIdx.x; i < 3 * E; i += blockDim.x) {
+      const int k = i % 3;
+      off[i] = elem[i] - (i < 3 * rc.P ? rc.tx_c[k] : rc.rx_c[k]);
+    }
   }
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int grp = static_cast<int>(blockIdx.z) * 4 + wave;
@@ -270,69 +295,85 @@ nufft_spread_kernel(
   float2 acc[kNuSlots];
 #pragma unroll
   for (int s = 0; s < kNuSlots; ++s) acc[s] = {0.0f, 0.0f};
+  // not staged: this lane's two elements
+  double at[3] = {}, ar[3] = {};
+  float at2 = 0.0f, ar2 = 0.0f;
+  if constexpr (!STAGED) {
+    if (!wave_on) return;
+    double t2 = 0.0, r2 = 0.0;
+    for (int k = 0; k < 3; ++k) {
+      at[k] = elem[3 * p + k] - rc.tx_c[k];
+      ar[k] = elem[3 * q + k] - rc.rx_c[k];
+      t2 += at[k] * at[k];
+      r2 += ar[k] * ar[k];
+    }
+    at2 = static_cast<float>(t2);
+    ar2 = static_cast<float>(r2);
+  }
   for (int b0 = rr.x; b0 < rr.y; b0 += batch) {
     const int nb = min(batch, rr.y - b0);
-    __syncthreads();  // the offsets are in; the last batch's readers are done
-    for (int i = threadIdx.x; i < nb * E; i += blockDim.x) {
-      const int rec = i / E, e = i - rec * E;
-      const NuRecF<INTRA> *r = srec + b0 + rec;
-      const bool tx = e < rc.P;
-      const double *u = tx ? r->ut : r->ur;
-      const double a[3] = {off[3 * e], off[3 * e + 1], off[3 * e + 2]};
-      double aa = 0.0;
-      for (int k = 0; k < 3; ++k) aa += a[k] * a[k];
-      const double s = u[0] * a[0] + u[1] * a[1] + u[2] * a[2];
-      const float dist = tx ? r->rt : r->rr;
-      const float sf = static_cast<float>(s);
-      const float h = fmaf(-sf, sf, static_cast<float>(aa));
-      const float rd = __builtin_amdgcn_rcpf(fmaf(-2.0f, sf, 2.0f * dist));
-      const float qd = h * rd;
-      const float ed = qd * fmaf(-qd, rd, 1.0f);
-      const float dR = ed - sf;
-      term[i] = {s, ed, dR};
-      if constexpr (INTRA) {
-        const float af[3] = {static_cast<float>(a[0]), static_cast<float>(a[1]),
-                             static_cast<float>(a[2])};
-        const float va = r->ext[0] * af[0] + r->ext[1] * af[1] + r->ext[2] * af[2];
-        rdot[i] = fmaf(dist, tx ? r->ext[3] : r->ext[4], -va) * __builtin_amdgcn_rcpf(dist + dR);
+    if constexpr (STAGED) {
+      __syncthreads();  // the offsets are in; the last batch's readers are done
+      for (int i = threadIdx.x; i < nb * E; i += blockDim.x) {
+        const int rec = i / E, e = i - rec * E;
+        const NuRecF<INTRA> *r = srec + b0 + rec;
+        const bool tx = e < rc.P;
+        const double *u = tx ? r->ut : r->ur;
+        const double a[3] = {off[3 * e], off[3 * e + 1], off[3 * e + 2]};
+        double aa = 0.0;
+        for (int k = 0; k < 3; ++k) aa += a[k] * a[k];
+        const float dist = tx ? r->rt : r->rr;
+        const ElemTerm T = element_term(u, dist, a, static_cast<float>(aa));
+        term[i] = T;
+        if constexpr (INTRA)
+          rdot[i] = element_rate(r->ext, tx ? r->ext[3] : r->ext[4], dist, T.dR, a);
       }
+      __syncthreads();
+      if (!wave_on) continue;
+      // a lane per record: the first cells of its blocks in this wave (sources at s[0], s[3],
+      // s[6]): the lowest cell within `reach` of the source's position for the wave's first
+      // channel, clamped to the blocks there are (the runs keep every channel's cells inside the
+      // window, so a clamp never drops one of them). Every channel of the wave lies within
+      // wave_d cells of the first.
+      if (lane < nb) {
+        const NuRecF<INTRA> *r = srec + b0 + lane;
+        const float dL = term[lane * E + p_first].dR + term[lane * E + q_first].dR;
+        float x0 = fmaf(kappa, dL, static_cast<float>(r->cell - rr.z) + r->frac);
+        if constexpr (INTRA) {
+          const float tdot = (rdot[lane * E + p_first] + rdot[lane * E + q_first]) * inv_c0;
+          float A, B;
+          x0 += doppler_shift(tdot, r->g1, r->ext[5], A, B);
+        }
+        int32_t starts = 0;
+        for (int j = 0; j < 3; ++j) {
+          const int lo = static_cast<int>(ceilf((x0 - r->s[3 * j]) - reach));
+          starts |= min(max(lo, 0), kNuTopStart) << (8 * j);
+        }
+        starts_of[lane] = starts;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
-    __syncthreads();
-    if (!wave_on) continue;
-    // a lane per record: the first cells of its blocks in this wave (sources at s[0], s[3],
-    // s[6]): the lowest cell within `reach` of the source's position for the wave's first
-    // channel, clamped to the blocks there are (the runs keep every channel's cells inside the
-    // window, so a clamp never drops one of them). Every channel of the wave lies within
-    // wave_d cells of the first.
-    if (lane < nb) {
-      const NuRecF<INTRA> *r = srec + b0 + lane;
-      const float dL = term[lane * E + p_first].dR + term[lane * E + q_first].dR;
-      float x0 = fmaf(kappa, dL, static_cast<float>(r->cell - rr.z) + r->frac);
-      if constexpr (INTRA) {
-        const float tdot = (rdot[lane * E + p_first] + rdot[lane * E + q_first]) * inv_c0;
-        float A, B;
-        x0 += doppler_shift(tdot, r->g1, r->ext[5], A, B);
-      }
-      int32_t starts = 0;
-      for (int j = 0; j < 3; ++j) {
-        const int lo = static_cast<int>(ceilf((x0 - r->s[3 * j]) - reach));
-        starts |= min(max(lo, 0), kNuTopStart) << (8 * j);
-      }
-      starts_of[lane] = starts;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+    using Head = std::conditional_t<STAGED, NuHead, NuRecF<INTRA>>;  // what a record is read of
     const auto *heads = reinterpret_cast<const unsigned char *>(srec + b0) +
-                        offsetof(NuRecF<INTRA>, g1);
+                        (STAGED ? offsetof(NuRecF<INTRA>, g1) : 0);
     const auto head = [&](int i) {
-      return load_uniform(reinterpret_cast<const NuHead *>(heads + i * sizeof(NuRecF<INTRA>)));
+      return load_uniform(reinterpret_cast<const Head *>(heads + i * sizeof(NuRecF<INTRA>)));
     };
     const ElemTerm *tp = term + p, *tq = term + q;
-    NuHead nxt = head(0);
+    Head nxt = head(0);
     for (int i = 0; i < nb; ++i) {
-      const NuHead r = nxt;
-      const ElemTerm T = tp[i * E], R = tq[i * E];
-      const uint32_t starts = __builtin_amdgcn_readfirstlane(starts_of[i]);
+      const Head r = nxt;
+      ElemTerm T, R;
+      uint32_t starts;
+      if constexpr (STAGED) {
+        T = tp[i * E];
+        R = tq[i * E];
+        starts = __builtin_amdgcn_readfirstlane(starts_of[i]);
+      } else {
+        T = element_term(r.ut, r.rt, at, at2);
+        R = element_term(r.ur, r.rr, ar, ar2);
+      }
       // this channel's path difference dL = -(s_t + s_r) + e_t + e_r, amplitude, phase and
       // grid position
       const float rel_c = static_cast<float>(r.cell - rr.z) + r.frac;
@@ -345,7 +386,13 @@ nufft_spread_kernel(
       if constexpr (INTRA) {
         // this channel's tau' (first order in the sample time), its Doppler shift relative
         // to the record's and the constant phase A M/2 + B M^2/4
-        const float tdot = (rdot[i * E + p] + rdot[i * E + q]) * inv_c0;
+        float rate;
+        if constexpr (STAGED)
+          rate = rdot[i * E + p] + rdot[i * E + q];
+        else
+          rate = element_rate(r.ext, r.ext[3], r.rt, T.dR, at) +
+                 element_rate(r.ext, r.ext[4], r.rr, R.dR, ar);
+        const float tdot = rate * inv_c0;
         float A, B;
         const float shift = doppler_shift(
             tdot, r.g1, load_uniform(&srec[b0 + i].ext[5]), A, B);
@@ -356,6 +403,14 @@ nufft_spread_kernel(
       t -= rintf(t);
       const float amp = __builtin_amdgcn_rcpf((r.rt + T.dR) * (r.rr + R.dR));
       const float qx = __builtin_amdgcn_cosf(t) * amp, qy = -__builtin_amdgcn_sinf(t) * amp;
+      if constexpr (!STAGED) {  // the blocks' first cells, a source a lane
+        const float x0 = __builtin_bit_cast(
+            float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, xr)));
+        const float off_l = lane == 0 ? r.s[0] : lane == 1 ? r.s[3] : r.s[6];
+        const int lo = min(max(static_cast<int>(ceilf((x0 - off_l) - reach)), 0), kNuTopStart);
+        starts = __builtin_amdgcn_readlane(lo, 0) | __builtin_amdgcn_readlane(lo, 1) << 8 |
+                 __builtin_amdgcn_readlane(lo, 2) << 16;
+      }
       // The next head is asked for when this record's LDS reads are in: one counter holds both
       // kinds of load, so a wait for the LDS would wait for the head, too.
       __builtin_amdgcn_sched_barrier(0);
@@ -424,23 +479,24 @@ size_t nufft_spread_smem_bytes(int elements, int batch, int waves, bool intra) {
 
 namespace {
 
-template <bool INTRA>
+template <bool INTRA, bool STAGED>
 hipError_t launch_spread_t(const DevScene &sc, const RadarConst &rc, const NuShape &ns,
                            const double *elem, const NuRecF<INTRA> *recs, const int4 *runs,
                            const int32_t *n_runs, float2 *part, const NuBatch &bt, dim3 grid,
                            dim3 blk, int ncell, hipStream_t s) {
-  const size_t lds = nufft_spread_smem_bytes(rc.P + rc.Q, ns.spread_batch, blk.x / 64, INTRA);
+  const size_t lds =
+      STAGED ? nufft_spread_smem_bytes(rc.P + rc.Q, ns.spread_batch, blk.x / 64, INTRA) : 0;
   switch (ncell) {
     case 14:
-      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 14>), grid, blk, lds, s, sc, rc, ns, elem,
+      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 14, STAGED>), grid, blk, lds, s, sc, rc, ns, elem,
                          recs, runs, n_runs, part, bt);
       break;
     case 16:
-      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 16>), grid, blk, lds, s, sc, rc, ns, elem,
+      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 16, STAGED>), grid, blk, lds, s, sc, rc, ns, elem,
                          recs, runs, n_runs, part, bt);
       break;
     case 20:
-      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 20>), grid, blk, lds, s, sc, rc, ns, elem,
+      hipLaunchKernelGGL((nufft_spread_kernel<INTRA, 20, STAGED>), grid, blk, lds, s, sc, rc, ns, elem,
                          recs, runs, n_runs, part, bt);
       break;
     default:
@@ -459,16 +515,27 @@ hipError_t launch_nufft_spread(const DevScene &sc, const RadarConst &rc, const N
   const int groups = (O + 63) / 64;
   const int per_block = groups < 4 ? groups : 4;
   NuShape ns = ns0;
-  ns.spread_batch = nufft_spread_batch(rc.P + rc.Q);
   dim3 sgrid(static_cast<unsigned>(ns.max_runs), static_cast<unsigned>(ns.n_chirps),
              static_cast<unsigned>((groups + 3) / 4));
   const dim3 blk(64 * per_block);
   const int ncell = nufft_cells_per_source(ns);
-  if (rc.intra)
-    return launch_spread_t<true>(sc, rc, ns, elem, static_cast<const NuRecF<true> *>(srec), runs,
-                                 n_runs, part, bt, sgrid, blk, ncell, s);
-  return launch_spread_t<false>(sc, rc, ns, elem, static_cast<const NuRecF<false> *>(srec), runs,
-                                n_runs, part, bt, sgrid, blk, ncell, s);
+  // Staged where a record has at most a quarter as many elements as the workgroup has lanes: with
+  // more, the terms cost as much as each lane's own two do, and their way through LDS comes on
+  // top. Staged against own terms, spreads of 2k to 60k facets by 8 or 64 chirps in parts of the
+  // time without either form's block tests in levels: 12 x 16 elements 0.76 and 0.81, 32 x 32
+  // 0.77 and 0.82, 8 x 8 0.72 and 0.74, 2 x 64 0.86 and 0.78, 64 x 1 0.96 and 0.73; with the delay
+  // within the chirp 12 x 16 0.82 and 0.82, 8 x 8 0.81 and 0.78, 64 x 1 1.09 and 0.77.
+  const bool staged = 4 * (rc.P + rc.Q) <= static_cast<int>(blk.x);
+  ns.spread_batch = staged ? nufft_spread_batch(rc.P + rc.Q) : 1024;  // or a whole run
+  const auto launch = [&](auto intra, auto stage) {
+    return launch_spread_t<intra(), stage()>(sc, rc, ns, elem,
+                                             static_cast<const NuRecF<intra()> *>(srec), runs,
+                                             n_runs, part, bt, sgrid, blk, ncell, s);
+  };
+  if (rc.intra) return staged ? launch(std::true_type{}, std::true_type{})
+                              : launch(std::true_type{}, std::false_type{});
+  return staged ? launch(std::false_type{}, std::true_type{})
+                : launch(std::false_type{}, std::false_type{});
 }
 
 }  // namespace rsim

@@ -79,7 +79,7 @@ struct NuShape {
   int32_t ng, ld, cb, groups;  // grid cells, LDS row stride, channels per FFT workgroup, groups
   int32_t n0, n_chirps;        // chirps of this launch: n0 .. n0 + n_chirps - 1
   int32_t spread_groups;       // 64-channel groups of the spread
-  int32_t spread_batch;        // records whose element terms the spread stages together
+  int32_t spread_batch;        // records the spread takes together (staged: their terms in LDS)
   int64_t rec_stride;          // records per chirp (forward: lit facets + points)
   double chan_d;               // largest grid offset of a channel from the phase-centre path
   double wave_d;               // largest grid offset of a channel from the first of its wave
