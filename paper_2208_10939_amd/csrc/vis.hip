@@ -12,7 +12,8 @@
 // Moller-Trumbore test keeps its precision). The lanes of a wave trace nearly the same rays, so
 // visibility walks a BVH once a wave: nodes and triangles in scalar registers, a mask of the
 // lanes inside each node, one small stack a wave. Bound by the chain of a wave's node fetches
-// and by its box tests. Against a walk per lane (32 node registers and an LDS stack column a
+// and by its box tests. Few chirps of many facets, where a wave would hold many different walks,
+// keep a walk per lane (launch_visibility has the rule). Against a walk per lane (32 node registers and an LDS stack column a
 // lane, 4 waves a SIMD): 50k facets x 128 chirps 433 -> 190 us, 30k x 64 235 -> 74 us, 20k x 81
 // with ground paths 565 -> 230 us, 1M x 256 15.0 -> 8.8 ms.
 #include <algorithm>
@@ -49,74 +50,9 @@ __device__ inline bool box_hit(const float *lo, const float *hi, float ox, float
   return tn <= tf;
 }
 
-// Any triangle of the leaf hit by o + t d, t in [kTEps, 1 - kTEps] (closed test)?
-__device__ inline bool leaf_hit(const float4 *leaf, int32_t ref, float ox, float oy, float oz,
-                                float dx, float dy, float dz, int32_t skip) {
-  uint32_t code = static_cast<uint32_t>(-ref - 1);
-  uint32_t first = code >> 4, count = code & 15u;
-  for (uint32_t k = 0; k < count; ++k) {
-    const float4 a = leaf[3 * (first + k) + 0];
-    const float4 b = leaf[3 * (first + k) + 1];
-    const float4 c = leaf[3 * (first + k) + 2];
-    if (__float_as_int(c.y) == skip) continue;
-    // v0 = a.xyz, e1 = (a.w, b.x, b.y), e2 = (b.z, b.w, c.x)
-    float e1x = a.w, e1y = b.x, e1z = b.y;
-    float e2x = b.z, e2y = b.w, e2z = c.x;
-    float px = dy * e2z - dz * e2y, py = dz * e2x - dx * e2z, pz = dx * e2y - dy * e2x;
-    float det = e1x * px + e1y * py + e1z * pz;
-    if (det == 0.0f) continue;
-    float inv = 1.0f / det;
-    float sx = ox - a.x, sy = oy - a.y, sz = oz - a.z;
-    float u = (sx * px + sy * py + sz * pz) * inv;
-    if (!(u >= 0.0f && u <= 1.0f)) continue;
-    float qx = sy * e1z - sz * e1y, qy = sz * e1x - sx * e1z, qz = sx * e1y - sy * e1x;
-    float v = (dx * qx + dy * qy + dz * qz) * inv;
-    if (!(v >= 0.0f && u + v <= 1.0f)) continue;
-    float t = (e2x * qx + e2y * qy + e2z * qz) * inv;
-    if (t >= kTEps && t <= 1.0f - kTEps) return true;
-  }
-  return false;
-}
-
 __device__ inline float safe_inv(float d) {
   const float tiny = 1e-30f;
   return 1.0f / (fabsf(d) > tiny ? d : copysignf(tiny, d));
-}
-
-// Any-hit traversal of one four-wide BLAS for the body-frame segment o -> o + d: leaves
-// are tested when their box is hit, the first hit inner child is entered next and the other
-// hit inner children (at most three per level) wait on the stack.
-__device__ bool blas_occluded(const BvhNode4 *nodes, const float4 *leaf, float ox, float oy,
-                              float oz, float dx, float dy, float dz, int32_t skip,
-                              int32_t *stack, int stride) {
-  const float ix = safe_inv(dx), iy = safe_inv(dy), iz = safe_inv(dz);
-  int sp = 0;
-  int32_t node = 0;
-  while (true) {
-    const BvhNode4 nd = nodes[node];
-    int32_t next = -1;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float lo[3] = {nd.lo[0][i], nd.lo[1][i], nd.lo[2][i]};
-      const float hi[3] = {nd.hi[0][i], nd.hi[1][i], nd.hi[2][i]};
-      if (!box_hit(lo, hi, ox, oy, oz, ix, iy, iz)) continue;
-      const int32_t c = nd.c[i];
-      if (c < 0) {
-        if (leaf_hit(leaf, c, ox, oy, oz, dx, dy, dz, skip)) return true;
-      } else if (next >= 0) {
-        stack[sp * stride] = c;  // <= 3 per level: stack_depth = 3 (depth + 1)
-        ++sp;
-      } else {
-        next = c;
-      }
-    }
-    if (next < 0) {
-      if (sp == 0) return false;
-      --sp;
-      next = stack[sp * stride];
-    }
-    node = next;
-  }
 }
 
 // A flat (horizontal) instance cannot block the segment c -> s: c lies no lower than its
@@ -127,60 +63,56 @@ __device__ inline bool flat_below(const DevInstance &I, const double c[3], doubl
   return I.flat && c[2] >= I.flat_lo && I.flat_hi - c[2] <= 0.5e-6 && s_z - c[2] >= 1.0;
 }
 
-// Is the world segment c -> s blocked by any triangle of the scene at time t
-// (triangle `self_local` of instance `self_inst` excluded)?
-__device__ bool segment_blocked(const DevScene &sc, double t, const double c[3],
-                                const double s[3], int self_inst, int32_t self_local,
-                                int32_t *stack, int stride, bool skip_plane = false,
-                                uint64_t cand = ~uint64_t(0)) {
-  double d[3] = {s[0] - c[0], s[1] - c[1], s[2] - c[2]};
-  // reciprocals once per segment (the boxes are padded, so the rounding of a product
-  // instead of a quotient cannot turn a hit box into a miss)
-  const double id[3] = {d[0] != 0.0 ? 1.0 / d[0] : 0.0, d[1] != 0.0 ? 1.0 / d[1] : 0.0,
-                        d[2] != 0.0 ? 1.0 / d[2] : 0.0};
-  for (int j = 0; j < sc.n_inst; ++j) {
-    if (j < 64 && !((cand >> j) & 1u)) continue;  // no segment of the wave meets its box
-    const DevInstance &I = sc.inst[j];
-    if (!I.has_bvh) continue;
-    if (skip_plane && I.in_plane) continue;  // the road surface under a reflected leg
-    if (flat_below(I, c, s[2])) continue;
-    double p[3] = {I.pos0[0] + I.vel[0] * t, I.pos0[1] + I.vel[1] * t, I.pos0[2] + I.vel[2] * t};
-    // world-space slab test against the instance box (FP64, conservative box)
-    double tn = 0.0, tf = 1.0;
-    bool miss = false;
-    for (int k = 0; k < 3; ++k) {
-      double lo = I.box_lo[k] + p[k], hi = I.box_hi[k] + p[k];
-      if (d[k] == 0.0) {
-        if (c[k] < lo || c[k] > hi) miss = true;
-        continue;
-      }
-      double a = (lo - c[k]) * id[k], b = (hi - c[k]) * id[k];
-      tn = fmax(tn, fmin(a, b));
-      tf = fmin(tf, fmax(a, b));
-    }
-    if (miss || tn > tf) continue;
-    // body frame: x_body = R^T (x - p)
-    const double *R = I.rot;
-    double q0 = c[0] - p[0], q1 = c[1] - p[1], q2 = c[2] - p[2];
-    float ox = static_cast<float>(R[0] * q0 + R[3] * q1 + R[6] * q2);
-    float oy = static_cast<float>(R[1] * q0 + R[4] * q1 + R[7] * q2);
-    float oz = static_cast<float>(R[2] * q0 + R[5] * q1 + R[8] * q2);
-    float dx = static_cast<float>(R[0] * d[0] + R[3] * d[1] + R[6] * d[2]);
-    float dy = static_cast<float>(R[1] * d[0] + R[4] * d[1] + R[7] * d[2]);
-    float dz = static_cast<float>(R[2] * d[0] + R[5] * d[1] + R[8] * d[2]);
-    int32_t skip = (j == self_inst) ? self_local : -1;
-    if (blas_occluded(I.nodes, I.leaf, ox, oy, oz, dx, dy, dz, skip, stack, stride)) return true;
-  }
-  return false;
-}
-
 struct LeafTriangle {
   float4 a, b, c;  // v0 = a.xyz, e1 = (a.w, b.x, b.y), e2 = (b.z, b.w, c.x), id = c.y
 };
 
-// Lanes of `in` whose segment o -> o + d[r] of some r hits a triangle of the leaf
-// (closed test, t in [kTEps, 1 - kTEps]). The roundings are spelled out: a segment through an
-// edge is decided by them, and the same segment is to be decided alike everywhere.
+// Does the segment o -> o + d[r] of some r hit the triangle (closed test, t in [kTEps, 1 - kTEps])?
+// The roundings are spelled out, those of one segment and of two as the compiler once chose them
+// (u's sum alone differs): a segment through an edge is decided by them.
+template <int NR>
+__device__ inline bool triangle_hit(const LeafTriangle &tr, float ox, float oy, float oz,
+                                    const float (&d)[NR][3]) {
+  const float e1x = tr.a.w, e1y = tr.b.x, e1z = tr.b.y;
+  const float e2x = tr.b.z, e2y = tr.b.w, e2z = tr.c.x;
+  const float sx = ox - tr.a.x, sy = oy - tr.a.y, sz = oz - tr.a.z;
+  const float qx = fmaf(sy, e1z, -(sz * e1y)), qy = fmaf(sz, e1x, -(sx * e1z)),
+              qz = fmaf(sx, e1y, -(sy * e1x));
+  bool hit = false;
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const float dx = d[r][0], dy = d[r][1], dz = d[r][2];
+    const float px = fmaf(dy, e2z, -(dz * e2y)), py = fmaf(dz, e2x, -(dx * e2z)),
+                pz = fmaf(dx, e2y, -(dy * e2x));
+    const float det = fmaf(e1z, pz, fmaf(e1x, px, e1y * py));
+    const float un = NR == 2 ? fmaf(sz, pz, fmaf(sy, py, sx * px))
+                             : fmaf(sz, pz, fmaf(sx, px, sy * py));
+    // clearly outside [0, 1], and no need for the quotient to see it (the bounds leave
+    // room for its rounding, and for one that underflows to zero)
+    const bool outside = un * det < -0x1p-100f || fabsf(un) > 1.0001f * fabsf(det);
+    if (hit || outside || det == 0.0f) continue;
+    const float inv = 1.0f / det;
+    const float u = un * inv;
+    if (!(u >= 0.0f && u <= 1.0f)) continue;
+    const float vn = fmaf(dz, qz, fmaf(dx, qx, dy * qy));
+    if (!(vn * inv >= 0.0f && fmaf(vn, inv, u) <= 1.0f)) continue;
+    const float t = fmaf(e2z, qz, fmaf(e2x, qx, e2y * qy)) * inv;
+    hit = t >= kTEps && t <= 1.0f - kTEps;
+  }
+  return hit;
+}
+
+// |d1 - d2| rounded up (FP32 sqrt is correctly rounded; the factor covers the rest): the boxes
+// are grown by it where two segments are walked as one.
+template <int NR>
+__device__ inline float walk_pad(const float (&d)[NR][3]) {
+  if constexpr (NR == 1) return 0.0f;
+  const float ex = d[0][0] - d[NR - 1][0], ey = d[0][1] - d[NR - 1][1],
+              ez = d[0][2] - d[NR - 1][2];
+  return __builtin_sqrtf(ex * ex + ey * ey + ez * ez) * 1.0001f + 1e-7f;
+}
+
+// Lanes of `in` with a segment that hits a triangle of the leaf.
 template <int NR>
 __device__ inline uint64_t packet_leaf(const float4 *leaf, int32_t ref, float ox, float oy,
                                        float oz, const float (&d)[NR][3], int32_t skip,
@@ -192,33 +124,8 @@ __device__ inline uint64_t packet_leaf(const float4 *leaf, int32_t ref, float ox
     const LeafTriangle tr =
         load_uniform(reinterpret_cast<const LeafTriangle *>(leaf) + (first + k));
     bool hit = false;
-    if (__builtin_amdgcn_inverse_ballot_w64(in) && __float_as_int(tr.c.y) != skip) {
-      const float e1x = tr.a.w, e1y = tr.b.x, e1z = tr.b.y;
-      const float e2x = tr.b.z, e2y = tr.b.w, e2z = tr.c.x;
-      const float sx = ox - tr.a.x, sy = oy - tr.a.y, sz = oz - tr.a.z;
-      const float qx = fmaf(sy, e1z, -(sz * e1y)), qy = fmaf(sz, e1x, -(sx * e1z)),
-                  qz = fmaf(sx, e1y, -(sy * e1x));
-#pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const float dx = d[r][0], dy = d[r][1], dz = d[r][2];
-        const float px = fmaf(dy, e2z, -(dz * e2y)), py = fmaf(dz, e2x, -(dx * e2z)),
-                    pz = fmaf(dx, e2y, -(dy * e2x));
-        const float det = fmaf(e1z, pz, fmaf(e1x, px, e1y * py));
-        const float un = NR == 2 ? fmaf(sz, pz, fmaf(sy, py, sx * px))
-                                 : fmaf(sz, pz, fmaf(sx, px, sy * py));
-        // clearly outside [0, 1], and no need for the quotient to see it (the bounds leave
-        // room for its rounding, and for one that underflows to zero)
-        const bool outside = un * det < -0x1p-100f || fabsf(un) > 1.0001f * fabsf(det);
-        if (hit || outside || det == 0.0f) continue;
-        const float inv = 1.0f / det;
-        const float u = un * inv;
-        if (!(u >= 0.0f && u <= 1.0f)) continue;
-        const float vn = fmaf(dz, qz, fmaf(dx, qx, dy * qy));
-        if (!(vn * inv >= 0.0f && fmaf(vn, inv, u) <= 1.0f)) continue;
-        const float t = fmaf(e2z, qz, fmaf(e2x, qx, e2y * qy)) * inv;
-        hit = t >= kTEps && t <= 1.0f - kTEps;
-      }
-    }
+    if (__builtin_amdgcn_inverse_ballot_w64(in) && __float_as_int(tr.c.y) != skip)
+      hit = triangle_hit<NR>(tr, ox, oy, oz, d);
     const uint64_t now = __ballot(hit);
     blocked |= now;
     in &= ~now;
@@ -239,12 +146,7 @@ __device__ uint64_t packet_occluded(const BvhNode4 *nodes, const float4 *leaf, f
                                     float oz, const float (&d)[NR][3], int32_t skip, uint64_t in,
                                     uint4 *stack) {
   const float ix = safe_inv(d[0][0]), iy = safe_inv(d[0][1]), iz = safe_inv(d[0][2]);
-  float pad = 0.0f;
-  if constexpr (NR == 2) {
-    const float ex = d[0][0] - d[1][0], ey = d[0][1] - d[1][1], ez = d[0][2] - d[1][2];
-    // |d1 - d2| rounded up (FP32 sqrt is correctly rounded; the factor covers the rest)
-    pad = __builtin_sqrtf(ex * ex + ey * ey + ez * ez) * 1.0001f + 1e-7f;
-  }
+  const float pad = walk_pad<NR>(d);
   uint64_t open = in, m = in;
   int sp = 0;
   int32_t node = 0;
@@ -286,30 +188,94 @@ __device__ uint64_t packet_occluded(const BvhNode4 *nodes, const float4 *leaf, f
   }
 }
 
-// Is the world segment c -> s[r] of some r blocked by a triangle of the scene at time t
-// (triangle `self_local` of instance `self_inst` excluded), for the lanes with `on`? All lanes
-// of the wave call it; the decisions are those of segment_blocked for each segment.
+// The same for one lane, in a walk of its own with a stack column of its own.
 template <int NR>
-__device__ bool packet_blocked(const DevScene &sc, bool on, double t, const double c[3],
-                               const double *const (&s)[NR], int self_inst, int32_t self_local,
-                               uint4 *stack, bool skip_plane, uint64_t cand) {
-  double dw[NR][3], idw[NR][3];  // reciprocals once per segment, as in segment_blocked
+__device__ bool lane_occluded(const BvhNode4 *nodes, const float4 *leaf, float ox, float oy,
+                              float oz, const float (&d)[NR][3], int32_t skip, int32_t *stack,
+                              int stride) {
+  const float ix = safe_inv(d[0][0]), iy = safe_inv(d[0][1]), iz = safe_inv(d[0][2]);
+  const float pad = walk_pad<NR>(d);
+  int sp = 0;
+  int32_t node = 0;
+  while (true) {
+    const BvhNode4 nd = nodes[node];
+    int32_t next = -1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float lo[3] = {nd.lo[0][i], nd.lo[1][i], nd.lo[2][i]};
+      const float hi[3] = {nd.hi[0][i], nd.hi[1][i], nd.hi[2][i]};
+      if (!box_hit(lo, hi, ox, oy, oz, ix, iy, iz, pad)) continue;
+      const int32_t c = nd.c[i];
+      if (c < 0) {
+        const uint32_t code = static_cast<uint32_t>(-c - 1);
+        const LeafTriangle *tr = reinterpret_cast<const LeafTriangle *>(leaf) + (code >> 4);
+        for (uint32_t k = 0; k < (code & 15u); ++k)
+          if (__float_as_int(tr[k].c.y) != skip && triangle_hit<NR>(tr[k], ox, oy, oz, d))
+            return true;
+      } else if (next >= 0) {
+        stack[sp * stride] = c;  // <= 3 per level: stack_depth = 3 (depth + 1)
+        ++sp;
+      } else {
+        next = c;
+      }
+    }
+    if (next < 0) {
+      if (sp == 0) return false;
+      --sp;
+      next = stack[sp * stride];
+    }
+    node = next;
+  }
+}
+
+// How a wave's lanes walk: together (stack: the wave's), or each for itself (stack: the lane's
+// column of int32, `stride` apart).
+struct PacketWalk {
+  uint4 *stack;
+  static constexpr bool kTogether = true;
+};
+struct LaneWalk {
+  int32_t *stack;
+  int stride;
+  static constexpr bool kTogether = false;
+};
+
+// Is the world segment c -> s[r] of some r blocked by a triangle of the scene at time t
+// (triangle `self_local` of instance `self_inst` excluded), for the lanes with `on`? All lanes of
+// the wave call it where they walk together.
+template <int NR, typename Walk>
+__device__ bool segments_blocked(const DevScene &sc, bool on, double t, const double c[3],
+                                 const double *const (&s)[NR], int self_inst, int32_t self_local,
+                                 const Walk &walk, bool skip_plane, uint64_t cand) {
+  if (!Walk::kTogether && !on) return false;
+  double dw[NR][3], idw[NR][3];
+  // reciprocals once per segment (the boxes are padded, so the rounding of a product
+  // instead of a quotient cannot turn a hit box into a miss)
   for (int r = 0; r < NR; ++r)
     for (int k = 0; k < 3; ++k) {
       dw[r][k] = s[r][k] - c[k];
       idw[r][k] = dw[r][k] != 0.0 ? 1.0 / dw[r][k] : 0.0;
     }
-  uint64_t open = __ballot(on);
+  uint64_t open = Walk::kTogether ? __ballot(on) : 0;
   const uint64_t all = open;
-  for (int j = 0; j < sc.n_inst && open; ++j) {
+  for (int j = 0; j < sc.n_inst; ++j) {
+    if (Walk::kTogether && !open) break;
     const DevInstance &I = sc.inst[j];
     if (!I.has_bvh) continue;
     if (skip_plane && I.in_plane) continue;  // the road surface under a reflected leg
-    // instances from 64 on are not filtered
-    uint64_t m = __ballot(j >= 64 || ((cand >> j) & 1u)) & open;
-    if (!m) continue;
+    // no segment of the facet over the group's chirps meets its box (instances from 64 on are
+    // not filtered)
+    const bool may = j >= 64 || ((cand >> j) & 1u);
+    uint64_t m = 0;
+    if constexpr (Walk::kTogether) {
+      m = __ballot(may) & open;
+      if (!m) continue;
+    } else if (!may) {
+      continue;
+    }
     bool below = true;
     for (int r = 0; r < NR; ++r) below = below && flat_below(I, c, s[r][2]);
+    if (!Walk::kTogether && below) continue;
     const double p[3] = {I.pos0[0] + I.vel[0] * t, I.pos0[1] + I.vel[1] * t,
                          I.pos0[2] + I.vel[2] * t};
     // world-space slab test of each segment against the instance box (FP64, conservative box)
@@ -329,8 +295,12 @@ __device__ bool packet_blocked(const DevScene &sc, bool on, double t, const doub
       }
       any = any || !(miss || tn > tf);
     }
-    m &= __ballot(any && !below);
-    if (!m) continue;
+    if constexpr (Walk::kTogether) {
+      m &= __ballot(any && !below);
+      if (!m) continue;
+    } else if (!any) {
+      continue;
+    }
     // body frame: x_body = R^T (x - p)
     const double *R = I.rot;
     const double q0 = c[0] - p[0], q1 = c[1] - p[1], q2 = c[2] - p[2];
@@ -342,9 +312,13 @@ __device__ bool packet_blocked(const DevScene &sc, bool on, double t, const doub
       for (int k = 0; k < 3; ++k)
         d[r][k] = static_cast<float>(R[k] * dw[r][0] + R[3 + k] * dw[r][1] + R[6 + k] * dw[r][2]);
     const int32_t skip = (j == self_inst) ? self_local : -1;
-    open &= ~packet_occluded<NR>(I.nodes, I.leaf, ox, oy, oz, d, skip, m, stack);
+    if constexpr (Walk::kTogether)
+      open &= ~packet_occluded<NR>(I.nodes, I.leaf, ox, oy, oz, d, skip, m, walk.stack);
+    else if (lane_occluded<NR>(I.nodes, I.leaf, ox, oy, oz, d, skip, walk.stack, walk.stride))
+      return true;
   }
-  return __builtin_amdgcn_inverse_ballot_w64(all & ~open);
+  if constexpr (Walk::kTogether) return __builtin_amdgcn_inverse_ballot_w64(all & ~open);
+  return false;
 }
 
 // Does the segment a -> b meet the box [lo, hi] (FP64 slab test, closed)?
@@ -405,19 +379,20 @@ __device__ bool candidate(const DevScene &sc, const RadarConst &rc, int64_t f, i
 // faces E and centroid -> E is clear; *reflected when the centroid lies above the ground
 // plane, the facet faces the image E' and both legs centroid -> S -> E are clear, S the
 // specular point (the road surface is skipped for these legs).
+template <typename Walk>
 __device__ void reflected_sides(const DevScene &sc, const RadarConst &rc, bool on, double t,
                                 const double c[3], const double n[3], const double E[3], double fe,
-                                int ii, int32_t lt, uint4 *stack, bool *direct, bool *refl) {
+                                int ii, int32_t lt, const Walk &walk, bool *direct, bool *refl) {
   const uint64_t every = ~uint64_t(0);
   const bool facing = on && fe > 0.0;
-  *direct = !packet_blocked<1>(sc, facing, t, c, {E}, ii, lt, stack, false, every) && facing;
+  *direct = !segments_blocked<1>(sc, facing, t, c, {E}, ii, lt, walk, false, every) && facing;
   const double ez = 2.0 * rc.z_ground - E[2];  // image height
   const double fi = n[0] * (E[0] - c[0]) + n[1] * (E[1] - c[1]) + n[2] * (ez - c[2]);
   bool clear = on && c[2] > rc.z_ground && fi > 0.0;
   const double a = (c[2] - rc.z_ground) / (c[2] - ez);
   const double S[3] = {c[0] + a * (E[0] - c[0]), c[1] + a * (E[1] - c[1]), rc.z_ground};
-  clear = !packet_blocked<1>(sc, clear, t, c, {S}, ii, lt, stack, true, every) && clear;
-  *refl = !packet_blocked<1>(sc, clear, t, S, {E}, -1, -1, stack, true, every) && clear;
+  clear = !segments_blocked<1>(sc, clear, t, c, {S}, ii, lt, walk, true, every) && clear;
+  *refl = !segments_blocked<1>(sc, clear, t, S, {E}, -1, -1, walk, true, every) && clear;
 }
 
 }  // namespace
@@ -427,9 +402,9 @@ namespace {
 // Lit decisions of facet f at chirp n: the single path (lit[0]) or, with the ground bounce,
 // the four path types (transmit side k & 1, receive side k >> 1). All lanes of the wave call
 // it; those without `on` get none.
-template <bool BOUNCE>
+template <bool BOUNCE, typename Walk>
 __device__ void facet_lit(const DevScene &sc, const RadarConst &rc, bool on, int64_t f, int n,
-                          uint4 *stack, uint64_t cand, bool lit[4]) {
+                          const Walk &walk, uint64_t cand, bool lit[4]) {
   lit[0] = lit[1] = lit[2] = lit[3] = false;
   const double t = n * rc.tc;
   const int ii = find_instance(sc.inst, sc.n_inst, f);
@@ -458,12 +433,13 @@ __device__ void facet_lit(const DevScene &sc, const RadarConst &rc, bool on, int
   if constexpr (!BOUNCE) {
     on = on && ft > 0.0 && fr > 0.0;
     if (__ballot(on))
-      lit[0] = !packet_blocked<2>(sc, on, t, c, {rc.tx_c, rc.rx_c}, ii, lt, stack, false, cand) && on;
+      lit[0] =
+          !segments_blocked<2>(sc, on, t, c, {rc.tx_c, rc.rx_c}, ii, lt, walk, false, cand) && on;
   } else {
     const double nv[3] = {nx, ny, nz};
     bool dt, it, dr, ir;
-    reflected_sides(sc, rc, on, t, c, nv, rc.tx_c, ft, ii, lt, stack, &dt, &it);
-    reflected_sides(sc, rc, on, t, c, nv, rc.rx_c, fr, ii, lt, stack, &dr, &ir);
+    reflected_sides(sc, rc, on, t, c, nv, rc.tx_c, ft, ii, lt, walk, &dt, &it);
+    reflected_sides(sc, rc, on, t, c, nv, rc.rx_c, fr, ii, lt, walk, &dr, &ir);
     lit[0] = dt && dr;
     lit[1] = it && dr;
     lit[2] = dt && ir;
@@ -478,7 +454,7 @@ __device__ void facet_lit(const DevScene &sc, const RadarConst &rc, bool on, int
 // nearly the same rays of one facet at neighbouring chirps and follow nearly one BVH path
 // (mapping lanes to neighbouring facets instead makes every wave walk the union of 64
 // different paths). Decisions are gathered as bits in LDS and written as whole bytes or words.
-template <bool BOUNCE>
+template <bool BOUNCE, typename Walk>
 __global__ void __launch_bounds__(2 * kVisThreads) __attribute__((amdgpu_waves_per_eu(4, 8)))
 vis_kernel(DevScene sc, RadarConst rc, int cw, int facets_per_block, int n_begin, int n_end) {
   extern __shared__ __align__(16) int32_t vis_lds[];
@@ -486,8 +462,11 @@ vis_kernel(DevScene sc, RadarConst rc, int cw, int facets_per_block, int n_begin
   const int words = max(1, facets_per_block >> 5);
   constexpr int types = BOUNCE ? 4 : 1;
   uint32_t *bits = reinterpret_cast<uint32_t *>(vis_lds);  // [types][cw][words]
-  uint4 *stack = reinterpret_cast<uint4 *>(vis_lds + kVisBitWords) +  // one per wave
-                 (threadIdx.x >> 6) * sc.stack_depth;
+  Walk walk;
+  if constexpr (Walk::kTogether)
+    walk = {reinterpret_cast<uint4 *>(vis_lds + kVisBitWords) + (threadIdx.x >> 6) * sc.stack_depth};
+  else
+    walk = {vis_lds + kVisBitWords + threadIdx.x, static_cast<int>(blockDim.x)};
   for (int k = threadIdx.x; k < types * cw * words; k += blockDim.x) bits[k] = 0u;
   const int nl = threadIdx.x % cw;
   const int n = n_begin + static_cast<int>(blockIdx.y) * cw + nl;
@@ -515,7 +494,7 @@ vis_kernel(DevScene sc, RadarConst rc, int cw, int facets_per_block, int n_begin
     const uint64_t cand =
         filter ? static_cast<uint64_t>(cand_lds[fl][1]) << 32 | cand_lds[fl][0] : ~uint64_t(0);
     bool lit[4];
-    facet_lit<BOUNCE>(sc, rc, on, min(f0 + fl, sc.n_facets - 1), min(n, n_end - 1), stack, cand, lit);
+    facet_lit<BOUNCE>(sc, rc, on, min(f0 + fl, sc.n_facets - 1), min(n, n_end - 1), walk, cand, lit);
     for (int k = 0; k < types; ++k)
       if (lit[k]) atomicOr(&bits[(k * cw + nl) * words + (fl >> 5)], 1u << (fl & 31));
   }
@@ -762,7 +741,8 @@ __device__ int32_t db_connect(const DevScene &sc, const RadarConst &rc, int64_t 
   // A lit facet (single path, this chirp's mask) faces both centres with both segments from
   // its centroid clear, the one to E among them: its test is not repeated
   const bool lit = (sc.mask[static_cast<int64_t>(n) * sc.mask_words + (f >> 5)] >> (f & 31)) & 1u;
-  if (!lit && segment_blocked(sc, t, ca, E, ia, la, stk, stride, false, cand_e)) return -1;
+  const LaneWalk walk{stk, stride};
+  if (!lit && segments_blocked<1>(sc, true, t, ca, {E}, ia, la, walk, false, cand_e)) return -1;
   // specular direction of d = (c_A - E) / |c_A - E|
   const double ld = sqrt(dot3(de, de));
   double r[3];
@@ -777,7 +757,8 @@ __device__ int32_t db_connect(const DevScene &sc, const RadarConst &rc, int64_t 
                         r[2] != 0.0 ? 1.0 / (r[2] * ray_len) : 0.0};
   const float t_min = static_cast<float>(1e-6 / ray_len);
   for (int j = 0; j < sc.n_inst; ++j) {
-    if (j < 64 && !((cand_r >> j) & 1u)) continue;  // no specular segment of the wave meets it
+    if (j < 64 && !((cand_r >> j) & 1u)) continue;  // no specular segment of the facet
+                                                    // over the group's chirps meets it
     const DevInstance &I = sc.inst[j];
     if (!I.has_bvh) continue;
     double p[3] = {I.pos0[0] + I.vel[0] * t, I.pos0[1] + I.vel[1] * t, I.pos0[2] + I.vel[2] * t};
@@ -823,7 +804,8 @@ __device__ int32_t db_connect(const DevScene &sc, const RadarConst &rc, int64_t 
   const double f1 = nb[0] * (ei[0] - h[0]) + nb[1] * (ei[1] - h[1]) + nb[2] * (ei[2] - h[2]);
   const double f2 = nb[0] * (O[0] - h[0]) + nb[1] * (O[1] - h[1]) + nb[2] * (O[2] - h[2]);
   if (!(f1 > 0.0) || !(f2 > 0.0)) return -1;
-  if (segment_blocked(sc, t, h, O, inst_best, id_best, stk, stride)) return -1;
+  if (segments_blocked<1>(sc, true, t, h, {O}, inst_best, id_best, walk, false, ~uint64_t(0)))
+    return -1;
   // footprint of A's tube on B's plane
   const double num = nb[0] * (cb[0] - ei[0]) + nb[1] * (cb[1] - ei[1]) + nb[2] * (cb[2] - ei[2]);
   double fp[3][3], cf[3] = {0.0, 0.0, 0.0};
@@ -954,34 +936,47 @@ hipError_t launch_visibility(const DevScene &sc, const RadarConst &rc, int n_beg
                              hipStream_t s) {
   if (sc.n_facets == 0 || n_chirps <= 0) return hipSuccess;
   if (n_begin < 0 || n_begin + n_chirps > rc.N) return hipErrorInvalidValue;
-  // Chirps per group: the smallest power of two >= the count, at most 64. A wave walks the union
-  // of the paths of its 64 / cw facets, which costs less than a pass for each once the passes
-  // fill the chip; below some 8192 passes idle lanes cost less than the longer walk (20k
-  // facets, 4 chirps: 235 us at cw 4, 72 at 32, 101 at 64; 500k facets, 8 chirps: 733 at cw 8,
-  // 1146 at 32).
-  int cw = 1;
+  // Chirps per group: the smallest power of two >= the count, at most 64.
+  int cw = 1, threads = kVisThreads, fpb = 8;
   while (cw < n_chirps && cw < 64) cw <<= 1;
   const auto chirp_groups = [&] { return (n_chirps + cw - 1) / cw; };
-  while (cw < 32 && sc.n_facets * cw < int64_t{64} * 8192) cw <<= 1;
-  int threads = kVisThreads, fpb = 8;
-  if (sc.n_facets * ((n_chirps + 63) / 64) <= 8192) {
-    // a wave's one chain of nodes is the time: one facet a wave (1k facets, 4 chirps: 24 us; 30
-    // at cw 32 with 256 threads. 30k facets, 64 chirps: 84, 74 with 256)
-    cw = 64;
-    threads = 2 * kVisThreads;
+  // Lanes that each walk for themselves where a wave's would hold the walks of many facets: one
+  // chirp and half a million facets or more (1.5M in 3 instances 2.3 ms, 2.7 together), with the
+  // ground's paths up to 4 chirps and two waves of them a SIMD (300k facets, one chirp: 0.36 ms,
+  // 0.62 together; 4 chirps 0.45, 0.60; 8 chirps 0.62, 0.59; 30k facets, 4 chirps 0.20, 0.15).
+  const int64_t lanes = sc.n_facets * cw;
+  const bool together = !(rc.bounce ? n_chirps <= 4 && lanes >= int64_t{120} << 10
+                                    : n_chirps == 1 && lanes >= int64_t{64} * 8192);
+  if (together) {
+    // A wave walks the union of the paths of its 64 / cw facets, which costs less than a pass for
+    // each once the passes fill the chip; below some 8192 passes idle lanes cost less than the
+    // longer walk (20k facets, 4 chirps: 235 us at cw 4, 72 at 32, 101 at 64; 500k facets, 8
+    // chirps: 733 at cw 8, 1146 at 32).
+    while (cw < 32 && sc.n_facets * cw < int64_t{64} * 8192) cw <<= 1;
+    if (sc.n_facets * ((n_chirps + 63) / 64) <= 8192) {
+      // a wave's one chain of nodes is the time: one facet a wave (1k facets, 4 chirps: 24 us; 30
+      // at cw 32 with 256 threads. 30k facets, 64 chirps: 84, 74 with 256)
+      cw = 64;
+      threads = 2 * kVisThreads;
+    }
+    // Facets per workgroup, 8, 16 or whole mask words: small ones even out the waves' work, large
+    // ones share the start of a workgroup (50k facets, 128 chirps: 190 us at 8, 232 at 32; 1M
+    // facets, 256 chirps: 9740 at 8, 8770 at 32)
+    while (fpb < 32 && sc.n_facets * chirp_groups() > int64_t{16384} * fpb) fpb *= 2;
+    fpb = std::max(fpb, threads / cw);
+  } else {
+    fpb = std::max(32, threads / cw);  // whole mask words, every thread busy for cw >= 8
   }
-  // Facets per workgroup, 8, 16 or whole mask words: small ones even out the waves' work, large
-  // ones share the start of a workgroup (50k facets, 128 chirps: 190 us at 8, 232 at 32; 1M
-  // facets, 256 chirps: 9740 at 8, 8770 at 32)
-  while (fpb < 32 && sc.n_facets * chirp_groups() > int64_t{16384} * fpb) fpb *= 2;
-  fpb = std::max(fpb, threads / cw);
   dim3 grid(static_cast<unsigned>((32 * sc.mask_words + fpb - 1) / fpb),
             static_cast<unsigned>(chirp_groups()));
   // bit words: types x cw x words <= 4 x 64 (fpb > 32 only with cw < 8)
-  const size_t lds = sizeof(int32_t) * kVisBitWords +
-                     sizeof(uint4) * (threads / 64) * static_cast<size_t>(sc.stack_depth);
-  hipLaunchKernelGGL(rc.bounce ? vis_kernel<true> : vis_kernel<false>, grid, dim3(threads), lds,
-                     s, sc, rc, cw, fpb, n_begin, n_begin + n_chirps);
+  const size_t stacks = together ? sizeof(uint4) * (threads / 64) : sizeof(int32_t) * threads;
+  const size_t lds = sizeof(int32_t) * kVisBitWords + stacks * static_cast<size_t>(sc.stack_depth);
+  const auto kernel =
+      together ? (rc.bounce ? vis_kernel<true, PacketWalk> : vis_kernel<false, PacketWalk>)
+               : (rc.bounce ? vis_kernel<true, LaneWalk> : vis_kernel<false, LaneWalk>);
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, s, sc, rc, cw, fpb, n_begin,
+                     n_begin + n_chirps);
   return hipGetLastError();
 }
 
