@@ -456,7 +456,8 @@ __device__ void facet_lit(const DevScene &sc, const RadarConst &rc, bool on, int
 // different paths). Decisions are gathered as bits in LDS and written as whole bytes or words.
 template <bool BOUNCE, typename Walk>
 __global__ void __launch_bounds__(2 * kVisThreads) __attribute__((amdgpu_waves_per_eu(4, 8)))
-vis_kernel(DevScene sc, RadarConst rc, int cw, int facets_per_block, int n_begin, int n_end) {
+vis_kernel(DevScene sc, RadarConst rc, int cw, int facets_per_block, bool find, int n_begin,
+           int n_end) {
   extern __shared__ __align__(16) int32_t vis_lds[];
   __shared__ uint32_t cand_lds[kVisThreads][2];
   const int words = max(1, facets_per_block >> 5);
@@ -471,9 +472,9 @@ vis_kernel(DevScene sc, RadarConst rc, int cw, int facets_per_block, int n_begin
   const int nl = threadIdx.x % cw;
   const int n = n_begin + static_cast<int>(blockIdx.y) * cw + nl;
   const int64_t f0 = static_cast<int64_t>(blockIdx.x) * facets_per_block;
-  // With several instances and the single path, the instances each facet's segments may meet
-  // are found first, a thread per (facet, instance), into LDS.
-  const bool filter = !BOUNCE && sc.n_inst > 1;
+  // The instances that each facet's segments may meet are found first where that pays
+  // (launch_visibility has the rule), a thread per (facet, instance), into LDS.
+  const bool filter = !BOUNCE && find;
   for (int k = threadIdx.x; k < 2 * facets_per_block; k += blockDim.x) (&cand_lds[0][0])[k] = 0u;
   __syncthreads();
   if (filter) {
@@ -967,6 +968,14 @@ hipError_t launch_visibility(const DevScene &sc, const RadarConst &rc, int n_beg
   } else {
     fpb = std::max(32, threads / cw);  // whole mask words, every thread busy for cw >= 8
   }
+  // The instance filter (single path) costs an FP64 test of swept boxes for each facet and
+  // instance, and saves one of each instance's box for every chirp: over 33 chirps or more it pays;
+  // over fewer only with many instances, from 17 chirps on (21 of 30k facets, 24 chirps: 1.19 ms,
+  // 1.30 without; 4 chirps 0.69, 0.52) or where few facets leave the chip waiting for the longest
+  // wave (21 of 1.5k, 4 chirps: 82 us, 92 without; 3 of 9.5k: 74, 63).
+  const bool filter = !rc.bounce && sc.n_inst > 1 &&
+                      (n_chirps > 32 ||
+                       (sc.n_inst > 8 && (n_chirps > 16 || sc.n_facets <= 32768)));
   dim3 grid(static_cast<unsigned>((32 * sc.mask_words + fpb - 1) / fpb),
             static_cast<unsigned>(chirp_groups()));
   // bit words: types x cw x words <= 4 x 64 (fpb > 32 only with cw < 8)
@@ -975,7 +984,7 @@ hipError_t launch_visibility(const DevScene &sc, const RadarConst &rc, int n_beg
   const auto kernel =
       together ? (rc.bounce ? vis_kernel<true, PacketWalk> : vis_kernel<false, PacketWalk>)
                : (rc.bounce ? vis_kernel<true, LaneWalk> : vis_kernel<false, LaneWalk>);
-  hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, s, sc, rc, cw, fpb, n_begin,
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, s, sc, rc, cw, fpb, filter, n_begin,
                      n_begin + n_chirps);
   return hipGetLastError();
 }
