@@ -2509,6 +2509,16 @@ int32_t rsim_autotune(rsim_ctx *ctx, const int32_t *scene_ids, int32_t n_scenes,
   if (!matrix_ineligible(ctx, rcn, RSIM_FP32_PHASE64)) cands.push_back({0, 0});
   for (const Cand c : {Cand{64, 16}, Cand{32, 16}, Cand{64, 8}, Cand{32, 8}, Cand{16, 16}})
     cands.push_back(c);
+  // The default tiles run as in a call that asks for none, cut where CUs are idle (spread_shape).
+  // An earlier choice, which such a call would take, is set aside meanwhile; it stays if the
+  // tuning fails.
+  struct Aside {
+    decltype(ctx->tuned) &tuned;
+    decltype(ctx->tuned)::node_type earlier;
+    ~Aside() {
+      if (earlier) tuned.insert(std::move(earlier));
+    }
+  } aside{ctx->tuned, ctx->tuned.extract(std::make_tuple(rcn.M, O, 0))};
   // each candidate runs once (cold); one within 1.5x of the best so far runs once more
   // and keeps the faster of its two facet-sum times
   float best = 1e30f;
@@ -2519,8 +2529,9 @@ int32_t rsim_autotune(rsim_ctx *ctx, const int32_t *scene_ids, int32_t n_scenes,
     rsim_opts o{};
     o.timing = 1;
     if (c.mb > 0) {
-      o.tile_m = c.mb;
-      o.tile_f = c.ft;
+      const bool by_default = c.mb == 64 && c.ft == 16;
+      o.tile_m = by_default ? 0 : c.mb;
+      o.tile_f = by_default ? 0 : c.ft;
       o.kernel = RSIM_KERNEL_VECTOR;
       const EchoShape sh = forward_shape(ctx, rcn, 0, c.mb, c.ft);
       if (echo_smem_bytes(0, c.mb, c.ft, sh) > ctx->max_lds) continue;
@@ -2556,6 +2567,7 @@ int32_t rsim_autotune(rsim_ctx *ctx, const int32_t *scene_ids, int32_t n_scenes,
     }
   }
   dev_free(ctx, echo);
+  aside.earlier = {};
   ctx->tuned[std::make_tuple(rcn.M, O, 0)] = best_s;
   ctx->version++;
   if (cache_json_path) {
