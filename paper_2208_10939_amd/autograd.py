@@ -21,13 +21,18 @@ class RadarRDM(torch.autograd.Function):
 
     @staticmethod
     def _load_geometry(sim: Simulator, scene_index: int, verts_np, vel_np):
-        """Upload this call's vertices and velocities into the library's scene."""
+        """Upload this call's vertices and velocities into the library's scene. Returns the
+        context's count of geometry changes as it is if no other caller made one since."""
         sid = sim.scene_ids[scene_index]
+        changes = sim.ctx.geometry_changes
         for mid, v in zip(sim.ctx.scene_meshes[sid], verts_np):
             sim.ctx.update_mesh(mid, v)
+            changes += 1
         pos0 = sim.inst_pos0[scene_index]
         for i in range(len(pos0)):
             sim.ctx.set_instance_motion(sid, i, pos0[i], vel_np[i])
+            changes += 1
+        return changes
 
     @staticmethod
     def forward(ctx, sim: Simulator, scene_index: int, vel, *verts):
@@ -35,7 +40,8 @@ class RadarRDM(torch.autograd.Function):
         meshes = sim.ctx.scene_meshes[sid]
         verts_np = [v.detach().cpu().numpy().copy() for v in verts]
         vel_np = vel.detach().cpu().numpy().copy()
-        RadarRDM._load_geometry(sim, scene_index, verts_np, vel_np)
+        # counted before the echo is computed: what another thread sets meanwhile is a change
+        ctx.geometry = RadarRDM._load_geometry(sim, scene_index, verts_np, vel_np)
         pos0 = sim.inst_pos0[scene_index]
         mask = sim.mask_buffer([scene_index])
         echo = sim.synthesize([scene_index], mask=mask, intra_chirp=sim.intra_chirp)
@@ -53,7 +59,6 @@ class RadarRDM(torch.autograd.Function):
         # loaded again where any vertices or motion were set since
         ctx.verts_np = verts_np
         ctx.vel_np = vel_np
-        ctx.geometry = sim.ctx.geometry_changes
         ctx.save_for_backward(mask, y)
         return rdm[0]
 
