@@ -95,10 +95,10 @@ __global__ void __launch_bounds__(256) cfar_kernel(const float *P, int N, int M,
 }
 
 // Row-major list of the detected cells of one cube (first max_points), and the count. One
-// workgroup a cube, kListCells consecutive cells a thread and step: a step costs a barrier and
-// a round trip to memory whatever it covers (131072 cells: 133 us at one cell a thread with
-// three barriers a step, 18 at 16 cells, 13 at 64).
-constexpr int kListCells = 64;
+// workgroup a cube, CELLS consecutive cells a thread and step: a step costs a barrier and a round
+// trip to memory whatever it covers, and a thread writes its cells one after the other
+// (launch_detect has the rule).
+template <int CELLS>
 __global__ void __launch_bounds__(1024) det_list_kernel(const uint8_t *det, int64_t NM,
                                                         int max_points, int32_t *list,
                                                         int32_t *count) {
@@ -108,18 +108,21 @@ __global__ void __launch_bounds__(1024) det_list_kernel(const uint8_t *det, int6
   int32_t *out = list + c * max_points;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int waves = blockDim.x >> 6;
-  const bool aligned = (reinterpret_cast<uintptr_t>(d) & 15) == 0;  // a thread's cells start at a multiple of 16
+  // a thread's cells start at a multiple of 16
+  static_assert(CELLS % 16 == 0 && CELLS <= 64, "whole vectors, one mask");
+  const bool aligned = (reinterpret_cast<uintptr_t>(d) & 15) == 0;
   int base = 0, buf = 0;
-  const int64_t step = static_cast<int64_t>(blockDim.x) * kListCells;
+  const int64_t step = static_cast<int64_t>(blockDim.x) * CELLS;
   for (int64_t k0 = 0; k0 < NM; k0 += step, buf ^= 1) {
-    const int64_t k = k0 + static_cast<int64_t>(threadIdx.x) * kListCells;
+    const int64_t k = k0 + static_cast<int64_t>(threadIdx.x) * CELLS;
     uint64_t hits = 0;  // bit j: cell k + j is detected
-    if (aligned && k + kListCells <= NM) {
-      uint4 v[kListCells / 16];
+    if (aligned && k + CELLS <= NM) {
+      constexpr int kQuads = CELLS / 16;
+      uint4 v[kQuads];
 #pragma unroll
-      for (int q = 0; q < kListCells / 16; ++q) v[q] = reinterpret_cast<const uint4 *>(d + k)[q];
+      for (int q = 0; q < kQuads; ++q) v[q] = reinterpret_cast<const uint4 *>(d + k)[q];
 #pragma unroll
-      for (int q = 0; q < kListCells / 16; ++q) {
+      for (int q = 0; q < kQuads; ++q) {
         const uint32_t w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
         if ((w[0] | w[1] | w[2] | w[3]) == 0) continue;
 #pragma unroll
@@ -127,7 +130,7 @@ __global__ void __launch_bounds__(1024) det_list_kernel(const uint8_t *det, int6
           hits |= ((w[j >> 2] >> (8 * (j & 3))) & 0xFFu) ? 1ull << (16 * q + j) : 0ull;
       }
     } else {
-      for (int j = 0; j < kListCells; ++j)
+      for (int j = 0; j < CELLS; ++j)
         if (k + j < NM && d[k + j]) hits |= 1ull << j;
     }
     const int mine = __popcll(hits);
@@ -369,7 +372,11 @@ hipError_t launch_detect(const float *rdm, const void *y, int64_t cubes, int O, 
   hipLaunchKernelGGL(cfar_kernel, dim3(static_cast<unsigned>(cubes * tiles_n * tiles_m)), dim3(256),
                      cfar_smem_bytes(gd, gr, td, tr), s, P, N, M, gd, gr, td, tr, scale,
                      1.0f / static_cast<float>(K), tiles_n, tiles_m, det, noise);
-  hipLaunchKernelGGL(det_list_kernel, dim3(static_cast<unsigned>(cubes)), dim3(1024), 0, s, det, NM,
+  // Few steps against few cells for a thread to write in turn: 16 cells a thread up to 32768 cells
+  // (two steps), 64 beyond. A whole call on 16 x 32 cells, all detected: 25 us at 16, 32 at 64 (29
+  // at one); 128 x 256: 30 and 32 (61); 256 x 512: 42 and 39 (156).
+  const auto det_list = NM <= 32768 ? det_list_kernel<16> : det_list_kernel<64>;
+  hipLaunchKernelGGL(det_list, dim3(static_cast<unsigned>(cubes)), dim3(1024), 0, s, det, NM,
                      max_points, list, count);
   AngleParams ap{O, N, M, na_x, na_z, n_nodes, max_points, 0, range_res, vel_res,
                  {c_ref[0], c_ref[1], c_ref[2]}};
