@@ -650,15 +650,17 @@ const char *nufft_common(const rsim_ctx *ctx, const RadarConst &rc, const rsim_o
   return nullptr;
 }
 
-// Channels per FFT workgroup: four workgroups per CU where the LDS allows (extra_lds:
-// bytes beyond the two row buffers).
-void nufft_fft_groups(const rsim_ctx *ctx, const RadarConst &rc, NuShape &s, size_t extra_lds) {
+// Channels per FFT workgroup: four workgroups per CU where the LDS allows at least min_cb
+// channels then, else two (extra_lds: bytes beyond the two row buffers).
+void nufft_fft_groups(const rsim_ctx *ctx, const RadarConst &rc, NuShape &s, size_t extra_lds,
+                      int min_cb) {
   s.cb = 0;
-  for (int cb = 16; cb >= 1 && !s.cb; --cb) {
-    NuShape t = s;
-    t.cb = cb;
-    if (nufft_smem_bytes(t) + extra_lds <= ctx->max_lds / 4) s.cb = cb;
-  }
+  for (int per_cu : {4, 2})
+    for (int cb = 16; cb >= (per_cu == 4 ? min_cb : 1) && !s.cb; --cb) {
+      NuShape t = s;
+      t.cb = cb;
+      if (nufft_smem_bytes(t) + extra_lds <= ctx->max_lds / per_cu) s.cb = cb;
+    }
   if (!s.cb) s.cb = 1;
   const int O = rc.P * rc.Q;
   s.cb = std::min(s.cb, O);
@@ -702,7 +704,7 @@ const char *nufft_adj_ineligible(const rsim_ctx *ctx, const RadarConst &rc, doub
   if (2.0 * r_max * s.kappa + s.chan_d + 0.5 * kNuWidth + 2.0 >= 0.5 * s.ng)
     return "facets too large for the NUFFT adjoint: node offsets (2 r_max df n_g / c) plus "
            "channel offsets reach half the grid";
-  nufft_fft_groups(ctx, rc, s, 0);
+  nufft_fft_groups(ctx, rc, s, 0, 1);
   *ns = s;
   return nullptr;
 }
@@ -1654,7 +1656,7 @@ int32_t rsim_synthesize(rsim_ctx *ctx, const int32_t *scene_ids, int32_t n_scene
     // the layout only grows while channels, grid and record size stay: calls on
     // smaller scenes reuse it, so captured graphs stay valid
     (void)0;
-    nufft_fft_groups(ctx, rcn, pl.ns, sizeof(int32_t) * max_runs);
+    nufft_fft_groups(ctx, rcn, pl.ns, sizeof(int32_t) * max_runs, 4);
     for (NuShape &si : pl.nu_scene) {
       si.cb = pl.ns.cb;
       si.groups = pl.ns.groups;
