@@ -650,21 +650,29 @@ const char *nufft_common(const rsim_ctx *ctx, const RadarConst &rc, const rsim_o
   return nullptr;
 }
 
-// Channels per FFT workgroup: four workgroups per CU where the LDS allows at least min_cb
-// channels then, else two (extra_lds: bytes beyond the two row buffers).
+// Channels per FFT workgroup: what a quarter of a CU's LDS holds (extra_lds: bytes beyond the two
+// row buffers), so four workgroups a CU. The forward's workgroups also find their cells' run
+// windows; where a quarter holds fewer than 4 channels to share them and there are rounds enough to
+// fill the chip anyway, they take half of the LDS. 192 channels, quarters and halves: 2000 cells x 16
+// chirps 136 and 117 us (12 workgroups a CU in quarters), 1024 x 32 182 and 171 (12), 864 x 64 157
+// and 140 (24), 864 x 16 60 and 78 (6); 64 channels, 768 x 96 60 and 66 (8).
 void nufft_fft_groups(const rsim_ctx *ctx, const RadarConst &rc, NuShape &s, size_t extra_lds,
-                      int min_cb) {
-  s.cb = 0;
-  for (int per_cu : {4, 2})
-    for (int cb = 16; cb >= (per_cu == 4 ? min_cb : 1) && !s.cb; --cb) {
+                      bool forward) {
+  const int O = rc.P * rc.Q;
+  const auto fit = [&](size_t lds) {
+    s.cb = 1;
+    for (int cb = 16; cb > 1 && s.cb == 1; --cb) {
       NuShape t = s;
       t.cb = cb;
-      if (nufft_smem_bytes(t) + extra_lds <= ctx->max_lds / per_cu) s.cb = cb;
+      if (nufft_smem_bytes(t) + extra_lds <= lds) s.cb = cb;
     }
-  if (!s.cb) s.cb = 1;
-  const int O = rc.P * rc.Q;
-  s.cb = std::min(s.cb, O);
-  s.groups = (O + s.cb - 1) / s.cb;
+    s.cb = std::min(s.cb, O);
+    s.groups = (O + s.cb - 1) / s.cb;
+  };
+  fit(ctx->max_lds / 4);
+  if (forward && s.cb < std::min(4, O) &&
+      static_cast<int64_t>(s.groups) * rc.N > int64_t{10} * ctx->cu_count)
+    fit(ctx->max_lds / 2);
 }
 
 // Why the NUFFT forward cannot run (nullptr: it can, and *ns holds its shape for facets
@@ -704,7 +712,7 @@ const char *nufft_adj_ineligible(const rsim_ctx *ctx, const RadarConst &rc, doub
   if (2.0 * r_max * s.kappa + s.chan_d + 0.5 * kNuWidth + 2.0 >= 0.5 * s.ng)
     return "facets too large for the NUFFT adjoint: node offsets (2 r_max df n_g / c) plus "
            "channel offsets reach half the grid";
-  nufft_fft_groups(ctx, rc, s, 0, 1);
+  nufft_fft_groups(ctx, rc, s, 0, false);
   *ns = s;
   return nullptr;
 }
@@ -1656,7 +1664,7 @@ int32_t rsim_synthesize(rsim_ctx *ctx, const int32_t *scene_ids, int32_t n_scene
     // the layout only grows while channels, grid and record size stay: calls on
     // smaller scenes reuse it, so captured graphs stay valid
     (void)0;
-    nufft_fft_groups(ctx, rcn, pl.ns, sizeof(int32_t) * max_runs, 4);
+    nufft_fft_groups(ctx, rcn, pl.ns, sizeof(int32_t) * max_runs, true);
     for (NuShape &si : pl.nu_scene) {
       si.cb = pl.ns.cb;
       si.groups = pl.ns.groups;

@@ -766,9 +766,8 @@ __device__ inline int lower_bound_lds(const int32_t *bases, int n, int v) {
 // deconvolution and the k_c^2 / k_m^2 factor on the M kept modes. Bound by the windows' way from
 // memory (50k facets, 128 chirps: 1.4 GB), so by the loads in flight: 16 a thread and groups of a
 // quarter of a CU's LDS, four to a CU, take 326 us where 8 and halves took 498 (16 and halves
-// 401, 8 and quarters 376, 16 and eighths 409). Rows of which a quarter holds fewer than 4 channels
-// keep halves: each group finds its cells' windows anew (60k facets twice, 2000 cells, 16 chirps:
-// 117 us in halves, 136 in quarters; 1024 cells, 32 chirps: 171, 182).
+// 401, 8 and quarters 376, 16 and eighths 409). Long rows, of which a quarter holds few, may take
+// halves (nufft_fft_groups has the rule).
 __global__ void __launch_bounds__(kNuFftThreads) nufft_fft_kernel(DevScene sc0, RadarConst rc,
                                                                 NuShape ns, NuBuffers nb,
                                                                 const float2 *tw, NuBatch bt) {
