@@ -24,8 +24,9 @@
 // Few chirps leave CUs without a workgroup, and a thread's serial chain (facets x MB samples)
 // is then the kernel's time. The cut forms (sh.chunk) give a workgroup one block of 64 or 192
 // channels and a thread a chunk of CH samples of it, whose phasors start from the block's by
-// the same steps: the same bits from up to 6 times the workgroups and MB / CH times the
-// threads. The host's spread_shape holds the rule and what both sides measured.
+// the same steps: the same bits from B_w times the workgroups, times the channel tiles (6 at 192
+// channels), and MB / CH times the threads. The host's spread_shape holds the rule and what both
+// sides measured.
 #include "echo_common.h"
 
 namespace rsim {

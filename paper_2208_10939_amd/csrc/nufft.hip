@@ -1278,9 +1278,9 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 // where a call has few workgroups, by a channel's chain of latencies. The elements' offsets lie in
 // LDS, the next channel's Rx element's are asked for a channel ahead, and a Tx element's terms
 // are kept for its channels. Three waves a SIMD: with four, which the registers would allow, a call
-// of some 3 workgroups a CU got 4 on some CUs and 2 on others. 192 channels, 48 chirps, kinds 1 (kind
-// 2 and 3), against every channel forming its own terms: 10k facets 434 -> 395 us (260 -> 240), 24k
-// 820 -> 755 (264 -> 243); offsets at four waves and not ahead took 507 (261) and 769 (266). The
+// of some 3 workgroups a CU got 4 on some CUs and 2 on others. 192 channels, 48 chirps, class 0
+// (class 1), against every channel forming its own terms: 10k facets 434 -> 395 us (260 -> 240),
+// 24k 820 -> 755 (264 -> 243); at four waves and not ahead 507 (261) and 769 (266). The
 // roundings are those of a channel's own terms, spelled out.
 template <int CLS>
 __global__ void __launch_bounds__(kNuGatherRecs) __attribute__((amdgpu_waves_per_eu(1, 3)))
